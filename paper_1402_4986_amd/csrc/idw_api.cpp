@@ -615,13 +615,14 @@ static int forward_impl(const idw_points* data, const idw_points* query, double 
   a.p = p;
   a.flags = flags;
   a.kahan = precision == IDW_FP32_KAHAN;
-  // Queries per lane: 2 for the FP32 sweeps whose weight takes at most one transcendental
-  // (p = 1, 2, 3, 4) and for every FP64 sweep (general p 1036 -> 957 ms at 1M x 1M; the
-  // others within 1.2%), 4 otherwise (the plan's default, which also sets the data split).
+  // Queries per lane: 2 for every FP64 sweep (general p 1036 -> 957 ms at 1M x 1M; the others
+  // within 1.2%).  FP32: 4 (the plan's default, which also sets the data split), 2-3% faster
+  // than 2 at 1M x 128K for every weight (p = 2: 19.28 against 19.75 ms; p = 2.5: 29.9 against
+  // 30.3; 3-D p = 3: 26.3 against 27.3), except where 4 would leave fewer than 2048 workgroups
+  // for the 1024 that are resident at once; relative weights and Kahan sums are built for 4.
   a.q_per_lane = w.qf;
   if (!(cfg && cfg->queries_per_lane) &&
-      (f64 || (precision == IDW_FP32 && p < kRelP &&
-               (a.pmode == PM_1 || a.pmode == PM_2 || a.pmode == PM_3 || a.pmode == PM_4))))
+      (f64 || (precision == IDW_FP32 && p < kRelP && cdiv(m, kWG * 4) * w.split_f < 2048)))
     a.q_per_lane = 2;
   // Large p in FP32: relative weights, sigma from each query's nearest distance.
   a.rel = !f64 && p >= kRelP;

@@ -200,8 +200,9 @@ __global__ __launch_bounds__(kWG) void kb_rmin(const BInst* __restrict__ inst, c
 // ---- persistent sweep ----
 template <int DIM, int PM, bool REL = false>
 __device__ __forceinline__ void kb_item(const BInst& I, const BItem& it, const double* __restrict__ hdr,
-                                        double2* __restrict__ part, P4<float> (*tile)[kTile],
+                                        double2* __restrict__ part, void* lds,
                                         const unsigned int* __restrict__ rmin) {
+  auto* tile = static_cast<RecTile<float, DIM, kTile>*>(lds);  // two tiles
   const int tid = threadIdx.x;
   const int64_t q0 = static_cast<int64_t>(it.qblock) * (kWG * kBQ);
   const int64_t jb = static_cast<int64_t>(it.chunk) * I.chunk;
@@ -250,7 +251,7 @@ __device__ __forceinline__ void kb_item(const BInst& I, const BItem& it, const d
         r.z = rr[u].z;
         r.w = 0.f;
       }
-      tile[b][u * kWG + tid] = r;
+      tile[b].put(u * kWG + tid, r);
     }
   };
   const int ntiles = static_cast<int>((je - jb + kTile - 1) / kTile);
@@ -269,7 +270,7 @@ __device__ __forceinline__ void kb_item(const BInst& I, const BItem& it, const d
   __syncthreads();
   for (int t = 0; t < ntiles; ++t) {
     if (t + 1 < ntiles) fetch(t + 1);
-    fwd_tile<float, DIM, PM, kBQ, false, 4, false, REL>(tile[t & 1], 0, kTile, qc, qi, I.nhp, sg, nacc, dacc);
+    fwd_tile_run<DIM, PM, kBQ, false, REL>(tile[t & 1], qc, I.nhp, sg, nacc, dacc);
     if (t + 1 < ntiles) put((t + 1) & 1);
     __syncthreads();
   }
@@ -296,11 +297,11 @@ __device__ __forceinline__ int kb_claim(int* __restrict__ counter, int* claim) {
   return w;  // uniform over the workgroup
 }
 
-__global__ __launch_bounds__(kWG) void kb_sweep(const BInst* __restrict__ inst, const BItem* __restrict__ items,
+__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4, 4))) void kb_sweep(const BInst* __restrict__ inst, const BItem* __restrict__ items,
                                                 int nitems, int* __restrict__ counter,
                                                 const double* __restrict__ hdr,
                                                 double2* __restrict__ part) {
-  __shared__ P4<float> tile[2][kTile];
+  alignas(16) __shared__ char tile[2 * sizeof(RecTile<float, 3, kTile>)];
   __shared__ int claim;
   for (;;) {
     const int w = kb_claim(counter, &claim);
@@ -332,12 +333,12 @@ __global__ __launch_bounds__(kWG) void kb_sweep(const BInst* __restrict__ inst, 
 
 // The work items of the relative-weight instances (p >= kRelP), scaled by each query's
 // nearest squared distance from kb_rmin.
-__global__ __launch_bounds__(kWG) void kb_sweep_rel(const BInst* __restrict__ inst,
+__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4, 4))) void kb_sweep_rel(const BInst* __restrict__ inst,
                                                     const BItem* __restrict__ items, int nitems,
                                                     int* __restrict__ counter, const double* __restrict__ hdr,
                                                     double2* __restrict__ part,
                                                     const unsigned int* __restrict__ rmin) {
-  __shared__ P4<float> tile[2][kTile];
+  alignas(16) __shared__ char tile[2 * sizeof(RecTile<float, 3, kTile>)];
   __shared__ int claim;
   for (;;) {
     const int w = kb_claim(counter, &claim);

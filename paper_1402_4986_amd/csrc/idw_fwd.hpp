@@ -18,6 +18,7 @@
 
 #include "idw_device.hpp"
 #include "idw_launch.hpp"
+#include "idw_phase.hpp"
 
 namespace idw {
 
@@ -89,7 +90,7 @@ struct KahanSum {
 // small, reaches the denominator.
 template <typename T, int DIM, int PM, int Q, bool DIAG, int UNR, bool KH = false, bool REL = false,
           bool TAIL = false, typename Acc>
-__device__ __forceinline__ void fwd_tile(const P4<T>* __restrict__ tl, int64_t jt, int cnt,
+__device__ __forceinline__ void fwd_tile(const RecTile<T, DIM, kTile>& tl, int64_t jt, int cnt,
                                          const T (&qc)[Q][3], const int64_t (&qi)[Q], T nhp,
                                          const T (&sg)[Q], Acc (&num)[Q], Acc (&den)[Q]) {
   constexpr int CH = 64;
@@ -97,7 +98,7 @@ __device__ __forceinline__ void fwd_tile(const P4<T>* __restrict__ tl, int64_t j
   if constexpr (KH) {
 #pragma unroll UNR
     for (int jj = 0; jj < lim; ++jj) {
-      const P4<T> d = tl[jj];
+      const P4<T> d = tl.get(jj);
       const T dv = (DIM == 3) ? d.w : d.z;
 #pragma unroll
       for (int k = 0; k < Q; ++k) {
@@ -123,7 +124,7 @@ __device__ __forceinline__ void fwd_tile(const P4<T>* __restrict__ tl, int64_t j
     const int ce = TAIL ? ((lim - c0) < CH ? (lim - c0) : CH) : CH;
 #pragma unroll UNR
     for (int jj = 0; jj < ce; ++jj) {
-      const P4<T> d = tl[c0 + jj];
+      const P4<T> d = tl.get(c0 + jj);
       const T dv = (DIM == 3) ? d.w : d.z;
 #pragma unroll
       for (int k = 0; k < Q; ++k) {
@@ -136,17 +137,6 @@ __device__ __forceinline__ void fwd_tile(const P4<T>* __restrict__ tl, int64_t j
         an[k] = fmaT(w, dv, an[k]);
         ad[k] += w;
       }
-      // 2-D, one reciprocal per pair, 2 queries per lane: ask the scheduler to interleave
-      // each transcendental with six other VALU instructions rather than issue them in
-      // runs (1M x 1M p = 2 forward: 179.0 -> 175.6 ms; in 3-D and with 4 queries per lane
-      // it measured slower, so those keep the default order).
-      if constexpr (sizeof(T) == 4 && DIM == 2 && Q == 2 && (PM == PM_1 || PM == PM_2)) {
-#pragma unroll
-        for (int k = 0; k < Q; ++k) {
-          __builtin_amdgcn_sched_group_barrier(0x002, 6, 0);  // 6 VALU
-          __builtin_amdgcn_sched_group_barrier(0x400, 1, 0);  // 1 transcendental
-        }
-      }
     }
 #pragma unroll
     for (int k = 0; k < Q; ++k) {
@@ -154,19 +144,67 @@ __device__ __forceinline__ void fwd_tile(const P4<T>* __restrict__ tl, int64_t j
       den[k].add(ad[k]);
     }
   };
-  // Unrolled over the tile, the compiler keeps every 64-record block's partial sums live
-  // until the tile's end and merges them there (159 VGPRs for the FP32 p = 2 sweep against
-  // 95 block by block).  Measured at 1M x 1M (16 data chunks): that is 3% faster for the
-  // one-transcendental FP32 weights (2-D p = 2: 188.4 against 193.7 ms; p = 1 and 3, and
-  // in 3-D, 4-6%) but slower where the weight needs two transcendentals or more registers:
-  // FP32 p = 4 (216.6 against 197.8 ms), p = 2.5 (302.0 against 279.2 ms; the 3-D
-  // mixture 87.5 against 81.2 ms) and the general-p exp2 / log2 (299.8 against 285.9 ms at
-  // p = 1.7), which go block by block.  FP64 differs by at most 2% either way.
-  if constexpr (PM == PM_GEN || (sizeof(T) == 4 && (PM == PM_4 || PM == PM_25))) {
+  // FP64 general p goes block by block; unrolled over the tile, the compiler keeps every
+  // 64-record block's partial sums live until the tile's end, which differs by at most 2%
+  // either way for the other FP64 weights.
+  if constexpr (PM == PM_GEN || sizeof(T) == 4) {
 #pragma unroll 1
     for (int c0 = 0; c0 < lim; c0 += CH) block(c0);
   } else {
     for (int c0 = 0; c0 < lim; c0 += CH) block(c0);
+  }
+}
+
+// A full tile in FP32 without a self pair: groups of 4 records, whose 4 Q weights form one
+// run of transcendentals (idw_phase.hpp).  The same operations in the same order per query
+// as fwd_tile, so the same bits.  Bound by instruction issue: 6 plain instructions and a
+// reciprocal per pair at p = 2, 20.6 cycles with the waves in step.  Against records read one
+// by one with the transcendentals between the plain instructions (3 waves per SIMD): 1M x 1M
+// p = 2 177 -> 154 ms; 3-D mixture, p = 2.5, 80.3 -> 66.8 ms; per-pair Kahan sums, p = 3,
+// 102,400 x 99,991, 3.95 -> 2.75 ms; the 64 batched instances 58.7 -> 45.0 ms.  Unrolled over
+// the whole 64-record block instead of 4 groups: within 0.3% in 2-D, 2-4% slower in 3-D.
+template <int DIM, int PM, int Q, bool KH, bool REL, typename Acc>
+__device__ __forceinline__ void fwd_tile_run(const RecTile<float, DIM, kTile>& tl, const float (&qc)[Q][3],
+                                             float nhp, const float (&sg)[Q], Acc (&num)[Q], Acc (&den)[Q]) {
+  constexpr int CH = 64, G = 4;
+#pragma unroll 1
+  for (int c0 = 0; c0 < kTile; c0 += CH) {
+    float an[Q], ad[Q];
+#pragma unroll
+    for (int k = 0; k < Q; ++k) an[k] = ad[k] = 0.f;
+#pragma unroll 4
+    for (int j = 0; j < CH; j += G) {
+      RecGroup<DIM, G> d;
+      d.load(tl, c0 + j);
+      float w[G * Q];
+#pragma unroll
+      for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int k = 0; k < Q; ++k) {
+          w[g * Q + k] = d.r2(qc[k], g);
+          if constexpr (REL) w[g * Q + k] *= sg[k];
+        }
+      weight_run<PM>(w, nhp);
+#pragma unroll
+      for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int k = 0; k < Q; ++k) {
+          if constexpr (KH) {
+            num[k].add(w[g * Q + k] * d.v[g]);
+            den[k].add(w[g * Q + k]);
+          } else {
+            an[k] = fmaf(w[g * Q + k], d.v[g], an[k]);
+            ad[k] += w[g * Q + k];
+          }
+        }
+    }
+    if constexpr (!KH) {
+#pragma unroll
+      for (int k = 0; k < Q; ++k) {
+        num[k].add(an[k]);
+        den[k].add(ad[k]);
+      }
+    }
   }
 }
 
@@ -180,40 +218,25 @@ __device__ __forceinline__ void fwd_finish(int64_t i, double num, double den, co
   out_flag[i] = route_of(den, hdr, false);
 }
 
-// Register-blocking and occupancy knobs of a sweep kernel: UNR = unroll of the per-record
-// loop, WPE = minimum waves per SIMD the register allocation must allow.
-// Values measured on MI355X (1M queries x 128K data, 2-D, p = 2): FP32 Q = 4 with a 4-deep
-// unroll issues 7.4 VALU lane-slots per pair against 8.3 for Q = 8.  With the 16-chunk
-// launch at 1M x 1M, Q = 2 (unroll 4) is faster still for the weights with at most one
-// transcendental (p = 2: 189.1 -> 179.0 ms; p = 3: 231.4 -> 223.2 ms; 3-D p = 2: 57.8 ->
-// 55.0 ms) and within 1% for p = 2.5 and general p, which keep Q = 4.  In FP64, Q = 2 is
-// faster for general p (1036 -> 957 ms) and within 1.2% elsewhere; the FP64 sweeps take it.
-// At Q = 2 a deeper unroll pays for p = 3 in 2-D (16-deep: 224.5 -> 214.4 ms; 3-D mixture
-// 66.5 -> 68.5 ms, so 3-D keeps 4) and for p = 4 (8-deep: 190.8 -> 188.3 ms, 3-D mixture
-// 60.6 -> 59.0 ms); for p = 1 and 2 and in FP64 it is 1-3% slower.  At Q = 4 an 8-deep
-// unroll pays for the per-pair Kahan sums (3-D mixture, p = 2.5: 130.5 -> 122.9 ms) and the
-// relative weights (2-D p = 8: 301.9 -> 285.2 ms) but not for the plain weights (2-D p = 1.5
-// 258.9 -> 263.2 ms, p = 2.5 279.1 -> 285.0 ms); the FP64 general-p sweep is faster 2-deep
-// (p = 1.7: 931 -> 894 ms, p = 2: 359 -> 364 ms, so only general p takes it).
-template <typename T, int Q, int PM = PM_GEN, int DIM = 2, bool KH = false, bool REL = false>
+// Register-blocking and occupancy knobs of a sweep kernel: UNR = unroll of the FP64
+// per-record loop, WMIN / WMAX = waves per SIMD the register allocation aims at.  FP32: an
+// even number of waves (idw_phase.hpp), 4, or 2 for the 8-query builds.  FP64 (1M x 1M): Q = 2
+// is faster than 4 for general p (1036 -> 957 ms) and within 1.2% elsewhere; general p is
+// faster 2-deep (p = 1.7: 931 -> 894 ms), the others 4-deep (p = 2: 359 against 364 ms).
+template <typename T, int Q, int PM = PM_GEN>
 struct SweepTune {
   static constexpr bool kF32 = sizeof(T) == 4;
-  static constexpr int UNR = Q >= 8                            ? 2
-                             : (kF32 && Q == 4 && (KH || REL)) ? 8
-                             : (!kF32 && Q == 2 && PM == PM_GEN) ? 2
-                             : (!kF32 || Q != 2)               ? 4
-                             : (PM == PM_3 && DIM == 2)        ? 16
-                             : PM == PM_4                      ? 8
-                                                               : 4;
-  static constexpr int WPE = 1;
+  static constexpr int UNR = PM == PM_GEN ? 2 : 4;
+  static constexpr int WMIN = kF32 ? (Q >= 8 ? 2 : 4) : 1;
+  static constexpr int WMAX = kF32 ? WMIN : 8;
 };
 
 // REL: relative weights; rmin holds each query's nearest squared distance (FP32 bits,
 // scaled units, from k_near_check over all queries) and the sums leave the kernel
 // multiplied by sigma^(p/2), i.e. in scaled units like those of the direct form.
-template <typename T, int DIM, int L, int PM, int Q, int UNR = SweepTune<T, Q, PM, DIM>::UNR,
-          int WPE = SweepTune<T, Q>::WPE, bool KH = false, bool REL = false>
-__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(WPE, 8))) void k_fwd_sweep(DevPts data, int64_t n, DevPts query, int64_t m,
+template <typename T, int DIM, int L, int PM, int Q, bool KH = false, bool REL = false,
+          typename Tune = SweepTune<T, Q, PM>>
+__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(Tune::WMIN, Tune::WMAX))) void k_fwd_sweep(DevPts data, int64_t n, DevPts query, int64_t m,
                                                    int64_t chunk, int split, T nhp, unsigned flags,
                                                    const double* __restrict__ hdr,
                                                    T* __restrict__ out_z,
@@ -222,7 +245,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(WPE, 8))) v
                                                    double2* __restrict__ part,
                                                    const unsigned long long* __restrict__ rmin,
                                                    double p) {
-  __shared__ P4<T> tile[2][kTile];
+  __shared__ RecTile<T, DIM, kTile> tile[2];
   const int tid = threadIdx.x;
   const int64_t q0 = static_cast<int64_t>(blockIdx.x) * (kWG * Q);
   const int64_t jb = static_cast<int64_t>(blockIdx.y) * chunk;
@@ -273,7 +296,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(WPE, 8))) v
   };
   auto put = [&](int b) {
 #pragma unroll
-    for (int u = 0; u < 2; ++u) tile[b][u * kWG + tid] = stage<T, DIM>(rc[u], rv[u], s);
+    for (int u = 0; u < 2; ++u) tile[b].put(u * kWG + tid, stage<T, DIM>(rc[u], rv[u], s));
   };
 
   const int ntiles = static_cast<int>((je - jb + kTile - 1) / kTile);
@@ -294,8 +317,10 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(WPE, 8))) v
         fwd_tile<T, DIM, PM, Q, false, 1, KH, REL, true>(tile[t & 1], jt, cnt, qc, qi, nhp, sg, nacc, dacc);
     } else if (diag) {
       fwd_tile<T, DIM, PM, Q, true, 1, KH, REL>(tile[t & 1], jt, kTile, qc, qi, nhp, sg, nacc, dacc);
+    } else if constexpr (sizeof(T) == 4) {
+      fwd_tile_run<DIM, PM, Q, KH, REL>(tile[t & 1], qc, nhp, sg, nacc, dacc);
     } else {
-      fwd_tile<T, DIM, PM, Q, false, UNR, KH, REL>(tile[t & 1], jt, kTile, qc, qi, nhp, sg, nacc, dacc);
+      fwd_tile<T, DIM, PM, Q, false, Tune::UNR, KH, REL>(tile[t & 1], jt, kTile, qc, qi, nhp, sg, nacc, dacc);
     }
     if (t + 1 < ntiles) put((t + 1) & 1);
     __syncthreads();
@@ -617,26 +642,17 @@ hipError_t launch_fwd_sweep_q(const FwdArgs& a, hipStream_t st) {
     hipLaunchKernelGGL((k_fwd_sweep<T, DIM, L, PM, QQ>), grid, dim3(kWG), 0, st, IDW_FWD_ARGS); \
     break;
   if constexpr (sizeof(T) == 4) {
-    using KK = SweepTune<T, 4, PM, DIM, true>;         // per-pair Kahan
-    using KR = SweepTune<T, 4, PM, DIM, false, true>;  // relative weights
-    using KKR = SweepTune<T, 4, PM, DIM, true, true>;
-    using K8 = SweepTune<T, 8>;
     if (a.rel) {  // relative weights: general-p form only
       if constexpr (PM == PM_GEN) {
         if (!a.rmin) return hipErrorInvalidValue;
-        if (a.kahan) {
-          if (Q != 4) return hipErrorInvalidValue;
-          hipLaunchKernelGGL((k_fwd_sweep<T, DIM, L, PM, 4, KKR::UNR, KKR::WPE, true, true>), grid, dim3(kWG), 0,
-                             st, IDW_FWD_ARGS);
-        } else if (Q == 4) {
-          hipLaunchKernelGGL((k_fwd_sweep<T, DIM, L, PM, 4, KR::UNR, KR::WPE, false, true>), grid, dim3(kWG), 0,
-                             st, IDW_FWD_ARGS);
-        } else if (Q == 8) {
-          hipLaunchKernelGGL((k_fwd_sweep<T, DIM, L, PM, 8, K8::UNR, K8::WPE, false, true>), grid, dim3(kWG), 0,
-                             st, IDW_FWD_ARGS);
-        } else {
+        if (a.kahan && Q == 4)
+          hipLaunchKernelGGL((k_fwd_sweep<T, DIM, L, PM, 4, true, true>), grid, dim3(kWG), 0, st, IDW_FWD_ARGS);
+        else if (!a.kahan && Q == 4)
+          hipLaunchKernelGGL((k_fwd_sweep<T, DIM, L, PM, 4, false, true>), grid, dim3(kWG), 0, st, IDW_FWD_ARGS);
+        else if (!a.kahan && Q == 8)
+          hipLaunchKernelGGL((k_fwd_sweep<T, DIM, L, PM, 8, false, true>), grid, dim3(kWG), 0, st, IDW_FWD_ARGS);
+        else
           return hipErrorInvalidValue;
-        }
         return hipGetLastError();
       } else {
         return hipErrorInvalidValue;
@@ -644,8 +660,7 @@ hipError_t launch_fwd_sweep_q(const FwdArgs& a, hipStream_t st) {
     }
     if (a.kahan) {  // per-pair Kahan variant, 4 queries per lane
       if (Q != 4) return hipErrorInvalidValue;
-      hipLaunchKernelGGL((k_fwd_sweep<T, DIM, L, PM, 4, KK::UNR, KK::WPE, true>), grid, dim3(kWG), 0, st,
-                         IDW_FWD_ARGS);
+      hipLaunchKernelGGL((k_fwd_sweep<T, DIM, L, PM, 4, true>), grid, dim3(kWG), 0, st, IDW_FWD_ARGS);
       return hipGetLastError();
     }
     switch (Q) {
