@@ -357,7 +357,10 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(Tune::WMIN,
 //                F_FP64, the others F_FP32 (their sweep results stand).
 // 5 VALU operations per pair (2 sub, mul + fma, min).
 constexpr int kNearGrid = 1024;      // workgroups of the nearest-distance check
-constexpr int kNearMinChunk = 8192;  // fewest data points per chunk
+// Fewest data points per chunk: one tile.  A few candidates (the common case from p = 2 on)
+// make one block, whose time is that of its chunk (131,072 or 1M points: 480 us with chunks of
+// 8192 points).
+constexpr int kNearMinChunk = kTile;
 
 template <typename T>
 __device__ __forceinline__ unsigned long long min_bits(T v) {  // v >= 0: bits order as values
