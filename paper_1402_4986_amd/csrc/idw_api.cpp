@@ -218,14 +218,14 @@ WsPlan plan_workspace(const idw_points* data, const idw_points* query, int preci
   w.qz = f64 ? 2 : 4;
   choose_split(m > 0 ? m : 1, cdiv(n, kWG * w.qz), 0, sizeof(double), n, w.split_z, w.chunk_z);
   // fused adjoint: workgroup (group, range) sweeps data range `range` for the query blocks
-  // group, group + G, ...: about 8192 workgroups in all (of 512 threads in FP32, 256 in
-  // FP64), for the reason given at choose_split (1M x 1M: 377.3 ms with 1024, 353.4 with
-  // 8192).  Ranges of at most 32K points (at least one tile) and as many groups as the
-  // query blocks allow, within kPartBudget for the dz rows (groups x n doubles) and for
-  // the query partials (ranges x m double4): 2 GB and 1 GB at n = m = 1M.
-  if (m > 0) {
+  // group, group + G, ...
+  if (m > 0 && f64) {
+    // about 8192 workgroups of 256 threads, for the reason given at choose_split: ranges of at
+    // most 32K points (at least one tile) and as many groups as the query blocks allow, within
+    // kPartBudget for the dz rows (groups x n doubles) and for the query partials (ranges x m
+    // double4).
     const int64_t target = 8192;
-    const int64_t nqb = cdiv(m, f64 ? 256 * 2 : 512 * 2);
+    const int64_t nqb = cdiv(m, 256 * 2);
     int64_t r = std::max<int64_t>(cdiv(n, 32768), cdiv(target, nqb));
     r = std::min<int64_t>(r, std::min<int64_t>(cdiv(n, kTile), std::max<int64_t>(1, kPartBudget / (32 * m))));
     r = std::min<int64_t>(r, 32768);  // grid y dimension
@@ -234,6 +234,21 @@ WsPlan plan_workspace(const idw_points* data, const idw_points* query, int preci
     w.fused_ranges = static_cast<int>(cdiv(n, w.fused_chunk));
     const int64_t gcap = std::min<int64_t>(nqb, std::max<int64_t>(1, kPartBudget / (8 * n)));
     w.fused_groups = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(gcap, cdiv(target, w.fused_ranges))));
+  } else if (m > 0) {
+    // about 4096 workgroups of 512 threads (8 rounds of the 512 that are resident), G and the
+    // ranges in the proportion that makes the partials' traffic, G n + 4 R m doubles written and
+    // read back, smallest; ranges of at least 4096 points (between two additions over the
+    // lanes) unless fewer than 1024 workgroups would be left; each array within kPartBudget.
+    const int64_t target = 4096;
+    const int64_t gcap = std::min<int64_t>(cdiv(m, 128), std::max<int64_t>(1, kPartBudget / (8 * n)));
+    const int64_t rcap = std::min<int64_t>({cdiv(n, kTile), std::max<int64_t>(1, kPartBudget / (32 * m)), 32768});
+    const double even = std::sqrt(4.0 * target * static_cast<double>(m) / static_cast<double>(n));
+    int64_t g = std::min<int64_t>(gcap, std::max<int64_t>(1, std::llround(std::min(even, 1e6))));
+    int64_t r = std::min<int64_t>(rcap, cdiv(target, g));
+    r = std::max<int64_t>(std::min<int64_t>(r, cdiv(n, 4096)), std::min<int64_t>(r, cdiv(1024, g)));
+    w.fused_chunk = cdiv(cdiv(n, r), kTile) * kTile;
+    w.fused_ranges = static_cast<int>(cdiv(n, w.fused_chunk));
+    w.fused_groups = static_cast<int>(std::min<int64_t>(gcap, std::max<int64_t>(g, cdiv(1024, w.fused_ranges))));
   }
   w.nbbox = static_cast<int>(std::min<int64_t>(1024, cdiv(n, kWG)));
   w.nwg_dp = static_cast<int>(cdiv(m, kWG));

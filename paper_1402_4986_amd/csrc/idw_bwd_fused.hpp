@@ -1,21 +1,21 @@
-// Fused FP32 adjoint sweep: the query-direction sums (P_i, G_i, for dp and dq) and the
+// Fused adjoint sweep: the query-direction sums (P_i, G_i, for dp and dq) and the
 // data-direction sums (dz_j = sum_i a_i w_ij, a_i = g_i / D_i, and, for the gradient with
 // respect to the data coordinates, X_j = sum_i a_i (w_ij / r2_ij)(z_j - Z_i)(q_i - x_j))
 // from ONE evaluation of each pair's weight.
 //
-// Lanes own Q queries each (registers).  Data points are staged in LDS in batches of 64,
-// each batch stored twice in a row, so that at step s lane L reads record (L + s) of the
-// doubled batch -- data point (L + s) mod 64 -- with a compile-time offset and no bank
-// conflicts.  Query-direction sums accumulate per lane as in the query sweep.  For the
+// FP64 (k_bwd_fused): lanes own Q queries each (registers).  Data points are staged in LDS in
+// batches of 64, each batch stored twice in a row, so that at step s lane L reads record
+// (L + s) of the doubled batch -- data point (L + s) mod 64 -- with a compile-time offset and
+// no bank conflicts.  Query-direction sums accumulate per lane as in the query sweep.  For the
 // data direction every lane forms s_L = sum_k a_k w_k for its point of the step, and a
-// running sum travels one lane per step (v_add_f32 with a wave_rol:1 DPP operand:
-// lane L receives the sum held by lane L+1), picking up the contribution of each lane for
-// the same data point.  After 64 steps lane L holds the sum over the wave's 64 x Q
-// queries for batch point (L - 1) mod 64.  That costs one DPP add per lane per step,
-// against a separate data sweep that recomputes every weight.  X_j rides the same rotation
-// with one running sum per coordinate.
+// running sum travels one lane per step (lane L receives the sum held by lane L+1), picking
+// up the contribution of each lane for the same data point.  After 64 steps lane L holds the
+// sum over the wave's 64 x Q queries for batch point (L - 1) mod 64.  X_j rides the same
+// rotation with one running sum per coordinate.
 //
-// Work decomposition: workgroup (qg, dr) sweeps data range dr for the query blocks
+// FP32 (k_bwd_fused32): lanes own data points and waves own queries, see there.
+//
+// Work decomposition of both: workgroup (qg, dr) sweeps data range dr for the query blocks
 // qg, qg + G, qg + 2G, ...; it writes the query partials of range dr (as the query sweep
 // with a data split) and accumulates its dz partial row qg across its query blocks (the
 // data sweep's split-over-queries format), so the existing fixed-order merges apply.
@@ -29,21 +29,12 @@ namespace idw {
 
 constexpr int kBatch = 64;  // data points per rotation batch (one wave)
 
-// Data points per LDS tile: 512 in FP32 (8 batches), 256 in FP64 (the records are twice as
-// wide; with 256-thread workgroups the tiles, batches doubled, and the per-wave sums take
-// 40 KB of LDS).
-template <typename T>
-struct FusedShape {
-  static constexpr int TILE = sizeof(T) == 8 ? 256 : 512;
-  static constexpr int NT = sizeof(T) == 8 ? 256 : 512;  // threads per workgroup
-};
-constexpr int kFTile = FusedShape<float>::TILE;
+// Data points per LDS tile and threads per workgroup of the FP64 form (the tiles, batches
+// doubled, and the per-wave sums take 40 KB of LDS).
+constexpr int kFTile64 = 256;
+constexpr int kFNT64 = 256;
 
-// Lane L takes the running sum of lane L+1 (wave rotate left by one); an FP64 value moves
-// as its two 32-bit halves.
-__device__ __forceinline__ float rotate_in(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x134, 0xF, 0xF, false));
-}
+// Lane L takes the running sum of lane L+1 (wave rotate left by one), as two 32-bit halves.
 __device__ __forceinline__ double rotate_in(double v) {
   const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
   const int lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(static_cast<unsigned int>(b)), 0x134, 0xF, 0xF, false);
@@ -56,13 +47,9 @@ __device__ __forceinline__ double rotate_in(double v) {
 // One 64-point batch.  MASK: some pairs must be skipped (padding records beyond the data
 // range, or the leave-one-out self pair); those get r2 = 1 and zero value factors.
 // Returns the dz running sum; with NDX, ax holds the X running sums.
-// REL: relative weights; the squared distance is multiplied by the query's sigma (sg)
-// before the weight terms, log2 r2 = log2(r2 sigma) - k (kq), and the X sums take the
-// coefficient a sigma (axq) so that they stay those of the direct form.
-template <typename T, int DIM, int PM, int Q, bool NDP, bool NDQ, bool NDX, bool MASK, int UNR, bool REL = false>
+template <typename T, int DIM, int PM, int Q, bool NDP, bool NDQ, bool NDX, bool MASK, int UNR>
 __device__ __forceinline__ T bwdf_batch(const P4<T>* __restrict__ rec, int lane, int64_t jb, int64_t je,
                                         bool excl, const T (&qc)[Q][3], const T (&zq)[Q], const T (&aq)[Q],
-                                        const T (&sg)[Q], const T (&kq)[Q], const T (&axq)[Q],
                                         const int64_t (&qi)[Q], T nhp, T (&ap)[Q], T (&ag)[Q][3], T (&ax)[3]) {
   T acc = T(0);
   ax[0] = ax[1] = ax[2] = T(0);
@@ -92,19 +79,15 @@ __device__ __forceinline__ T bwdf_batch(const P4<T>* __restrict__ rec, int lane,
       }
       T c = dv - zq[k];
       T a = aq[k];
-      T av = REL ? axq[k] : a;
-      if constexpr (REL) r2 *= sg[k];
       if constexpr (MASK) {
         if (!valid || (excl && j == qi[k])) {
           r2 = T(1);
           c = T(0);
           a = T(0);
-          av = T(0);
         }
       }
       T w, f = T(0), lg = T(0);
       wterms<PM, NDQ || NDX, NDP, PowTab<T, PM, NDP || NDX>::on>(r2, nhp, w, f, lg);
-      if constexpr (REL && NDP) lg -= kq[k];
       const T t = w * c;
       if constexpr (NDP) ap[k] = fmaT(t, lg, ap[k]);
       if constexpr (NDQ || NDX) {
@@ -115,7 +98,7 @@ __device__ __forceinline__ T bwdf_batch(const P4<T>* __restrict__ rec, int lane,
           if constexpr (DIM == 3) ag[k][2] = fmaT(u, dz, ag[k][2]);
         }
         if constexpr (NDX) {
-          const T v = av * u;
+          const T v = a * u;
           sx[0] = (k == 0) ? v * dx : fmaT(v, dx, sx[0]);
           sx[1] = (k == 0) ? v * dy : fmaT(v, dy, sx[1]);
           if constexpr (DIM == 3) sx[2] = (k == 0) ? v * dz : fmaT(v, dz, sx[2]);
@@ -132,27 +115,20 @@ __device__ __forceinline__ T bwdf_batch(const P4<T>* __restrict__ rec, int lane,
   return acc;
 }
 
-// Defaults measured on MI355X (1M queries x 256K data, 2-D, p = 2): 512-thread workgroups,
-// Q = 2, unroll 2, about 1024 workgroups in the grid: 13.6 VALU lane-slots per pair, against
-// 17.3 with 256-thread workgroups and 512 in the grid.
-constexpr int kFNT = FusedShape<float>::NT;
-
 // Coordinate given to queries that are left out of a sweep (flagged for the FP64 fix-up):
 // far from every scaled data point, yet with r2 (< 3 * 2^120) and every product of the
 // pair terms finite, so that their zero factors a = 0 give exact zeros.
 constexpr float kFarF = 0x1p60f;
 
-// T = float: the FP32 adjoint (with relative weights for large p); T = double: the FP64
-// adjoint (the FP64 one-step and table forms of the weights, no relative weights).
-template <typename T, int DIM, int L, int PM, int Q, bool NDP, bool NDQ, bool NDX, bool REL = false, int UNR = 2,
-          int WPE = 2, int NT = FusedShape<T>::NT>
+// The FP64 adjoint (the FP64 one-step and table forms of the weights).
+template <typename T, int DIM, int L, int PM, int Q, bool NDP, bool NDQ, bool NDX, int UNR = 2, int WPE = 2,
+          int NT = kFNT64>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE, 8))) void k_bwd_fused(
     DevPts data, int64_t n, DevPts query, int64_t m, int64_t chunk, int groups, T nhp, unsigned flags,
     const double* __restrict__ hdr, const T* __restrict__ saved_z, const T* __restrict__ grad_out,
     const double* __restrict__ saved_den, double4* __restrict__ part_q, double* __restrict__ part_z,
-    double* __restrict__ part_x, const uint8_t* __restrict__ route, double pd) {
-  static_assert(sizeof(T) == 4 || !REL, "FP64: no relative weights");
-  constexpr int kFTile = FusedShape<T>::TILE;
+    double* __restrict__ part_x, const uint8_t* __restrict__ route) {
+  constexpr int kFTile = kFTile64;
   constexpr int kFBatches = kFTile / kBatch;
   __shared__ P4<T> tile[2][2 * kFTile];   // batches stored twice in a row
   constexpr int PPT = kFTile / NT;        // tile points staged per thread
@@ -203,7 +179,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE, 8))) vo
   int first = 1;
   for (int64_t qb = qg; qb < nqb; qb += groups, first = 0) {
     const int64_t q0 = qb * qpb;
-    T qc[Q][3], zq[Q], aq[Q], sg[Q], kq[Q], axq[Q];
+    T qc[Q][3], zq[Q], aq[Q];
     int64_t qi[Q];
 #pragma unroll
     for (int k = 0; k < Q; ++k) {
@@ -212,9 +188,6 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE, 8))) vo
       bool ok = false;
       zq[k] = T(0);
       aq[k] = T(0);
-      sg[k] = T(1);
-      kq[k] = T(0);
-      axq[k] = T(0);
       if (qi[k] < m) {
         ok = route[qi[k]] == F_FP32;  // the others are left to the FP64 fix-up
         if (ok) {
@@ -222,17 +195,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE, 8))) vo
           Loader<T, DIM, L>::query(query, qi[k], c);
           zq[k] = saved_z[qi[k]];
           const double g = static_cast<double>(grad_out[qi[k]]);
-          if constexpr (REL) {
-            double E = 1.0;
-            float sgf = 1.f, kqf = 0.f;
-            rel_from_den(D / unit, pd, sgf, kqf, E);
-            sg[k] = sgf;
-            kq[k] = kqf;
-            aq[k] = static_cast<T>(g / E);
-            axq[k] = static_cast<T>(g / E * static_cast<double>(sgf));
-          } else {
-            aq[k] = static_cast<T>(g / (D / unit));
-          }
+          aq[k] = static_cast<T>(g / (D / unit));
         }
       }
 #pragma unroll
@@ -266,11 +229,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE, 8))) vo
         const int64_t jbat = jt + b * kBatch;
         T zs, ax[3];
         if (diag || tail)
-          zs = bwdf_batch<T, DIM, PM, Q, NDP, NDQ, NDX, true, 1, REL>(rec, lane, jbat, je, excl, qc, zq, aq, sg, kq,
-                                                                     axq, qi, nhp, ap, ag, ax);
+          zs = bwdf_batch<T, DIM, PM, Q, NDP, NDQ, NDX, true, 1>(rec, lane, jbat, je, excl, qc, zq, aq, qi, nhp, ap, ag, ax);
         else
-          zs = bwdf_batch<T, DIM, PM, Q, NDP, NDQ, NDX, false, UNR, REL>(rec, lane, jbat, je, excl, qc, zq, aq, sg,
-                                                                        kq, axq, qi, nhp, ap, ag, ax);
+          zs = bwdf_batch<T, DIM, PM, Q, NDP, NDQ, NDX, false, UNR>(rec, lane, jbat, je, excl, qc, zq, aq, qi, nhp, ap, ag, ax);
         const int at = b * kBatch + ((lane + kBatch - 1) & (kBatch - 1));
         zred[wave][at] = zs;
         if constexpr (NDX) {
@@ -335,6 +296,444 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE, 8))) vo
   }
 }
 
+// ---------------------------------------------------------------------------------------
+// FP32 form.  Lanes own data points, waves own queries: a wave holds R queries as uniform
+// (scalar) values and sweeps the data range 64 points at a time.  The data-direction sums of
+// a lane's point are then plain per-lane sums over the R queries, and the query-direction
+// sums are kept per lane and query (R (1 + DIM) registers) and added over the 64 lanes only
+// every kFlush points.  Nothing crosses lanes per pair: the rotation of the FP64 form costs
+// half a DPP add per pair, which also puts the SIMD's waves out of step (idw_phase.hpp;
+// measured 10 cycles per pair).  2-D p = 2 with dz, dp and dq: 11 plain instructions and two
+// transcendentals, 39.2 cycles per pair and wave at best, 41.7 for the loop body alone, 44.2
+// for the kernel; 1M x 1M: 350 ms with lanes owning queries and the rotation, 309 ms now; with
+// dx 462 -> 391, p = 1.5 404 -> 335, p = 8 (relative weights) 458 -> 402.
+// ---------------------------------------------------------------------------------------
+
+// w, f and log2(r2) of N pairs (wterms), their transcendentals in one run.
+template <int PM, bool NDQ, bool NDP, int N>
+__device__ __forceinline__ void wterms_run(const float (&r2)[N], float nhp, float (&w)[N], float (&f)[N],
+                                           float (&lg)[N]) {
+  run_begin();
+  if constexpr (PM == PM_GEN) {
+    const float e = NDQ ? nhp - 1.0f : nhp;
+#pragma unroll
+    for (int i = 0; i < N; ++i) lg[i] = __builtin_amdgcn_logf(r2[i]);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < N; ++i) f[i] = e * lg[i];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < N; ++i) f[i] = __builtin_amdgcn_exp2f(f[i]);
+  } else {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      if constexpr (PM == PM_2 || PM == PM_4)
+        w[i] = __builtin_amdgcn_rcpf(r2[i]);
+      else
+        w[i] = __builtin_amdgcn_rsqf(r2[i]);
+    }
+    if constexpr (NDP) {
+#pragma unroll
+      for (int i = 0; i < N; ++i) lg[i] = __builtin_amdgcn_logf(r2[i]);
+    }
+    if constexpr (PM == PM_25) {
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < N; ++i) f[i] = __builtin_amdgcn_sqrtf(w[i]);
+    }
+  }
+  run_end();
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    if constexpr (PM == PM_GEN) {
+      w[i] = NDQ ? f[i] * r2[i] : f[i];
+    } else if constexpr (PM == PM_2) {
+      f[i] = w[i];
+    } else if constexpr (PM == PM_1) {
+      f[i] = w[i] * w[i];
+    } else if constexpr (PM == PM_3) {
+      f[i] = w[i] * w[i];
+      w[i] = f[i] * w[i];
+    } else if constexpr (PM == PM_4) {
+      f[i] = w[i];
+      w[i] = w[i] * w[i];
+    } else {  // PM_25
+      const float s2 = w[i] * w[i];
+      w[i] = s2 * f[i];
+      f[i] = s2;
+    }
+  }
+}
+
+// Queries per wave: as many as the registers of 4 waves per SIMD hold.  16 in 2-D (48 sums) and
+// in 3-D (64 sums; 131,072 x 1M points, p = 2: 47.0 ms against 49.0 with 8); 8 where the scales
+// of the relative weights or the 3-D X sums would make 16 spill.
+template <int DIM, bool NDX, bool REL>
+struct FusedRows {
+  static constexpr int R = REL || (DIM == 3 && NDX) ? 8 : 16;
+};
+constexpr int kFusedWaves = 8;
+constexpr int kFlush = 4096;  // data points between the sums over lanes (64 per lane)
+
+__device__ __forceinline__ float read_lane(float v, int l) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l));
+}
+__device__ __forceinline__ double shfl_xor64(double v, int x) {
+  const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+  const int lo = __shfl_xor(static_cast<int>(static_cast<unsigned int>(b)), x);
+  const int hi = __shfl_xor(static_cast<int>(static_cast<unsigned int>(b >> 32)), x);
+  return __builtin_bit_cast(double, (static_cast<unsigned long long>(static_cast<unsigned int>(hi)) << 32) |
+                                        static_cast<unsigned int>(lo));
+}
+
+template <int DIM, int L, int PM, bool NDP, bool NDQ, bool NDX, bool REL, bool EXCL,
+          int R = FusedRows<DIM, NDX, REL>::R>
+__global__ __launch_bounds__(64 * kFusedWaves) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_bwd_fused32(
+    DevPts data, int64_t n, DevPts query, int64_t m, int64_t chunk, int groups, float nhp, unsigned,
+    const double* __restrict__ hdr, const float* __restrict__ saved_z, const float* __restrict__ grad_out,
+    const double* __restrict__ saved_den, double4* __restrict__ part_q, double* __restrict__ part_z,
+    double* __restrict__ part_x, const uint8_t* __restrict__ route, double pd) {
+  constexpr int NT = 64 * kFusedWaves;
+  constexpr int TILE = NT;                      // one point staged and folded per thread
+  constexpr int NB = TILE / 64;                 // 64-point batches per tile
+  constexpr int GQ = 4;                         // queries whose weights are taken in one run
+  constexpr int NC = (NDP ? 1 : 0) + (NDQ ? DIM : 0);  // query-direction sums per query
+  constexpr int NR = (R * NC + 7) / 8;          // rounds of 8 sums in the addition over lanes
+  static_assert(R % 8 == 0 && R <= 64 && (NB & (NB - 1)) == 0, "whole runs of queries");
+  __shared__ RecTile<float, 3, TILE> tile[2];
+  __shared__ float zred[kFusedWaves][TILE];     // per-wave dz sums of the tile; rows of the addition over lanes
+  __shared__ float xred[NDX ? kFusedWaves : 1][NDX ? DIM * TILE : 1];  // per-wave X sums
+  // the FP64 sums over lanes, in registers where LDS is taken by the X sums
+  constexpr bool LSUM = !NDX && NR > 0;
+  __shared__ double lsum[LSUM ? kFusedWaves : 1][LSUM ? NR : 1][LSUM ? 64 : 1];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int qg = blockIdx.x;
+  const int64_t jb = static_cast<int64_t>(blockIdx.y) * chunk;
+  const int64_t je = (jb + chunk < n) ? jb + chunk : n;
+  const float s = static_cast<float>(hdr[H_SCALE]);
+  const double unit = hdr[H_DEN_UNIT];
+  constexpr int64_t qpb = kFusedWaves * R;
+  const int64_t nqb = (m + qpb - 1) / qpb;
+  const int ntiles = static_cast<int>((je - jb + TILE - 1) / TILE);
+  double* zrow = part_z + static_cast<int64_t>(qg) * n;
+  double* xrow = NDX ? part_x + static_cast<int64_t>(qg) * n * DIM : nullptr;
+
+  float rc[3], rv;
+  auto fetch = [&](int t) {
+    const int64_t j = jb + static_cast<int64_t>(t) * TILE + tid;
+    rc[0] = rc[1] = rc[2] = rv = 0.f;
+    if (j < je) Loader<float, DIM, L>::data(data, j, rc, rv);
+  };
+  auto put = [&](int b) {
+    tile[b].put(tid, P4<float>{rc[0] * s, rc[1] * s, DIM == 3 ? rc[2] * s : 0.f, rv});
+  };
+
+  int first = 1;
+  for (int64_t qb = qg; qb < nqb; qb += groups, first = 0) {
+    const int64_t q0 = qb * qpb;
+    const int64_t qw = q0 + static_cast<int64_t>(wave) * R;  // this wave's first query
+    // lane r prepares query r, then every lane reads it as a uniform value
+    auto prepare = [&](float (&vq)[3], float& vz, float& va, float& vs, float& vk, float& vx) {
+      const int64_t i = qw + lane;
+      float c[3] = {0.f, 0.f, 0.f};
+      bool ok = false;
+      vz = va = vk = vx = 0.f;
+      vs = 1.f;
+      if (lane < R && i < m) {
+        ok = route[i] == F_FP32;  // the others are left to the FP64 fix-up
+        if (ok) {
+          const double D = saved_den[i];
+          Loader<float, DIM, L>::query(query, i, c);
+          vz = saved_z[i];
+          const double g = static_cast<double>(grad_out[i]);
+          if constexpr (REL) {
+            double E = 1.0;
+            rel_from_den(D / unit, pd, vs, vk, E);
+            va = static_cast<float>(g / E);
+            vx = static_cast<float>(g / E * static_cast<double>(vs));
+          } else {
+            vx = va = static_cast<float>(g / (D / unit));
+          }
+        }
+      }
+#pragma unroll
+      for (int d = 0; d < 3; ++d) vq[d] = ok ? c[d] * s : kFarF;
+    };
+    float vq[3], vz, va, vs, vk, vx;
+    prepare(vq, vz, va, vs, vk, vx);
+    float qc[R][3], zq[R], aq[R], sg[R], kq[R], axq[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+#pragma unroll
+      for (int d = 0; d < DIM; ++d) qc[r][d] = read_lane(vq[d], r);
+      zq[r] = read_lane(vz, r);
+      aq[r] = read_lane(va, r);
+      if constexpr (REL) {
+        sg[r] = read_lane(vs, r);
+        if constexpr (NDP) kq[r] = read_lane(vk, r);
+        if constexpr (NDX) axq[r] = read_lane(vx, r);
+      }
+    }
+    constexpr int NA = NC > 0 ? NC : 1;
+    float acc[NA][R];           // P, then G per coordinate
+    double sums[LSUM || NR == 0 ? 1 : NR];
+    float own[NA];              // EXCL, lane r: query r's sums over its leave-one-out block
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      own[c] = 0.f;
+#pragma unroll
+      for (int r = 0; r < R; ++r) acc[c][r] = 0.f;
+    }
+#pragma unroll
+    for (int k = 0; k < NR; ++k) {
+      if constexpr (LSUM)
+        lsum[wave][k][lane] = 0.0;
+      else
+        sums[k] = 0.0;
+    }
+
+    // The lane's point against the wave's queries.  Every layer of GQ independent operations
+    // is kept together: an operation on the result of the one before it would not issue
+    // beside the other wave's.
+    auto batch = [&](const P4<float>& d, float& zs, float (&xs)[3]) {
+#define IDW_LAYER(expr)                      \
+  __builtin_amdgcn_sched_barrier(0);         \
+  _Pragma("unroll") for (int i = 0; i < GQ; ++i) { expr; }
+#pragma unroll
+      for (int r0 = 0; r0 < R; r0 += GQ) {
+        float dx[GQ], dy[GQ], dz[GQ], r2[GQ], w[GQ], f[GQ], lg[GQ], c[GQ];
+        IDW_LAYER(dx[i] = qc[r0 + i][0] - d.x)
+        IDW_LAYER(dy[i] = qc[r0 + i][1] - d.y)
+        IDW_LAYER(r2[i] = dx[i] * dx[i])
+        if constexpr (DIM == 3) { IDW_LAYER(dz[i] = qc[r0 + i][2] - d.z) }
+        IDW_LAYER(r2[i] = fmaf(dy[i], dy[i], r2[i]))
+        if constexpr (DIM == 3) { IDW_LAYER(r2[i] = fmaf(dz[i], dz[i], r2[i])) }
+        if constexpr (REL) { IDW_LAYER(r2[i] *= sg[r0 + i]) }
+        wterms_run<PM, NDQ || NDX, NDP, GQ>(r2, nhp, w, f, lg);
+        IDW_LAYER(c[i] = d.w - zq[r0 + i])
+        if constexpr (REL && NDP) { IDW_LAYER(lg[i] -= kq[r0 + i]) }
+#pragma unroll
+        for (int i = 0; i < GQ; ++i) zs = fmaf(aq[r0 + i], w[i], zs);
+        if constexpr (NDP || PM != PM_GEN) { IDW_LAYER(w[i] = w[i] * c[i]) }
+        if constexpr (NDP) { IDW_LAYER(acc[0][r0 + i] = fmaf(w[i], lg[i], acc[0][r0 + i])) }
+        if constexpr (NDQ || NDX) {
+          IDW_LAYER(f[i] = wr_times<PM>(w[i], c[i], f[i]))  // (w / r2)(z - Z)
+          if constexpr (NDQ) {
+            constexpr int G0 = NDP ? 1 : 0;
+            IDW_LAYER(acc[G0][r0 + i] = fmaf(f[i], dx[i], acc[G0][r0 + i]))
+            IDW_LAYER(acc[G0 + 1][r0 + i] = fmaf(f[i], dy[i], acc[G0 + 1][r0 + i]))
+            if constexpr (DIM == 3) { IDW_LAYER(acc[G0 + 2][r0 + i] = fmaf(f[i], dz[i], acc[G0 + 2][r0 + i])) }
+          }
+          if constexpr (NDX) {
+            IDW_LAYER(f[i] = (REL ? axq[r0 + i] : aq[r0 + i]) * f[i])
+#pragma unroll
+            for (int i = 0; i < GQ; ++i) {
+              xs[0] = fmaf(f[i], dx[i], xs[0]);
+              xs[1] = fmaf(f[i], dy[i], xs[1]);
+              if constexpr (DIM == 3) xs[2] = fmaf(f[i], dz[i], xs[2]);
+            }
+          }
+        }
+      }
+#undef IDW_LAYER
+    };
+
+    // Leave-one-out: the lanes whose points are the wave's own queries against those queries,
+    // one query at a time, the self pair left out.
+    auto near_self = [&](const P4<float>& d, int self, float& zs, float (&xs)[3]) {
+      float vq[3], vz, va, vs, vk, vx;
+      prepare(vq, vz, va, vs, vk, vx);
+#pragma unroll 1
+      for (int r = 0; r < R; ++r) {
+        const float o[8] = {read_lane(vq[0], r), read_lane(vq[1], r), read_lane(vq[2], r), read_lane(vz, r),
+                            read_lane(va, r),    read_lane(vs, r),    read_lane(vk, r),    read_lane(vx, r)};
+        float p[NA];
+#pragma unroll
+        for (int c = 0; c < NA; ++c) p[c] = 0.f;
+        if (self >= 0 && self != r) {
+          float dx = o[0] - d.x, dy = o[1] - d.y, dz = 0.f;
+          float r2 = dx * dx;
+          r2 = fmaf(dy, dy, r2);
+          if constexpr (DIM == 3) {
+            dz = o[2] - d.z;
+            r2 = fmaf(dz, dz, r2);
+          }
+          if constexpr (REL) r2 *= o[5];
+          float w, f = 0.f, lg = 0.f;
+          wterms<PM, NDQ || NDX, NDP>(r2, nhp, w, f, lg);
+          if constexpr (REL && NDP) lg -= o[6];
+          const float c = d.w - o[3];
+          const float t = w * c;
+          const float u = wr_times<PM>(t, c, f);
+          zs = fmaf(o[4], w, zs);
+          if constexpr (NDP) p[0] = t * lg;
+          if constexpr (NDQ) {
+            constexpr int G0 = NDP ? 1 : 0;
+            p[G0] = u * dx;
+            p[G0 + 1] = u * dy;
+            if constexpr (DIM == 3) p[G0 + 2] = u * dz;
+          }
+          if constexpr (NDX) {
+            const float v = (REL ? o[7] : o[4]) * u;
+            xs[0] = fmaf(v, dx, xs[0]);
+            xs[1] = fmaf(v, dy, xs[1]);
+            if constexpr (DIM == 3) xs[2] = fmaf(v, dz, xs[2]);
+          }
+        }
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+          float v = p[c];
+#pragma unroll
+          for (int x = 1; x < 64; x <<= 1) v += __shfl_xor(v, x);
+          own[c] += lane == r ? v : 0.f;
+        }
+      }
+    };
+
+    // Adds the per-lane sums over the lanes: 8 of them at a time go through this wave's row of
+    // zred as 8 rows of 64, of which lane l adds 8 values of row l / 8 into its FP64 sum.
+    auto flush = [&]() {
+      float* row = zred[wave];
+#pragma unroll
+      for (int k = 0; k < NR; ++k) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const int e = 8 * k + i;
+          if (e < R * NC) {
+            row[i * 64 + lane] = acc[e / R][e % R];
+            acc[e / R][e % R] = 0.f;
+          }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        const P4<float> a = *reinterpret_cast<const P4<float>*>(&row[lane * 8]);
+        const P4<float> b = *reinterpret_cast<const P4<float>*>(&row[lane * 8 + 4]);
+        const double v = static_cast<double>(((a.x + a.y) + (a.z + a.w)) + ((b.x + b.y) + (b.z + b.w)));
+        if constexpr (LSUM)
+          lsum[wave][k][lane] += v;  // this lane's own element
+        else
+          sums[k] += v;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+      }
+    };
+
+    fetch(0);
+    put(0);
+    __syncthreads();
+    for (int t = 0; t < ntiles; ++t) {
+      if (t + 1 < ntiles) fetch(t + 1);
+      const int64_t jt = jb + static_cast<int64_t>(t) * TILE;
+      const auto& tl = tile[t & 1];
+      const int cnt = static_cast<int>(je - jt < TILE ? je - jt : TILE);  // points of the tile
+      // where the wave's own queries lie among them (leave-one-out)
+      const int64_t at = qw - jt;
+      const bool diag = EXCL && at < TILE && at > -R;
+      const int selfat = diag ? static_cast<int>(at) : TILE;
+      const bool plain = cnt == TILE && !diag;
+      const int64_t j = jt + tid;
+      double zold = 0.0;  // this thread's element of the dz row, loaded ahead
+      if (!first && j < je) zold = zrow[j];
+      P4<float> d = tl.get(lane);
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        const P4<float> dn = tl.get(((b + 1) & (NB - 1)) * 64 + lane);
+        const int pt = b * 64 + lane;
+        float zs = 0.f, xs[3] = {0.f, 0.f, 0.f};
+        uint64_t on = ~uint64_t(0);  // the lanes that take part
+        if (!plain)
+          on = __ballot(pt < cnt && static_cast<unsigned>(pt - selfat) >= static_cast<unsigned>(R));
+        if (__builtin_amdgcn_inverse_ballot_w64(on)) batch(d, zs, xs);
+        zred[wave][pt] = zs;
+        if constexpr (NDX) {
+#pragma unroll
+          for (int e = 0; e < DIM; ++e) xred[wave][e * TILE + pt] = xs[e];
+        }
+        d = dn;
+      }
+      if (EXCL && diag) {  // the points that the loop left out
+#pragma unroll 1
+        for (int b = 0; b < NB; ++b) {
+          const int pt = b * 64 + lane;
+          const int self = static_cast<unsigned>(pt - selfat) < static_cast<unsigned>(R) && pt < cnt ? pt - selfat : -1;
+          if (!__any(self >= 0)) continue;
+          float zs = 0.f, xs[3] = {0.f, 0.f, 0.f};
+          near_self(tl.get(pt), self, zs, xs);
+          if (self >= 0) {
+            zred[wave][pt] = zs;
+            if constexpr (NDX) {
+#pragma unroll
+              for (int e = 0; e < DIM; ++e) xred[wave][e * TILE + pt] = xs[e];
+            }
+          }
+        }
+      }
+      __syncthreads();  // zred complete; tile t fully consumed
+      // dz: add the waves' sums in a fixed order and fold into this group's row.  The stores
+      // come after the next tile has been put: a wait for its loads, which were issued before
+      // them, would otherwise wait for the stores too.
+      auto waves = [&](const float* v, int stride) {
+        return static_cast<double>(((v[0] + v[stride]) + (v[2 * stride] + v[3 * stride])) +
+                                   ((v[4 * stride] + v[5 * stride]) + (v[6 * stride] + v[7 * stride])));
+      };
+      zold += waves(&zred[0][tid], TILE);
+      double xv[3];
+      if constexpr (NDX) {
+#pragma unroll
+        for (int e = 0; e < DIM; ++e) xv[e] = waves(&xred[0][e * TILE + tid], DIM * TILE);
+      }
+      if (t + 1 < ntiles) put((t + 1) & 1);
+      __syncthreads();
+      if (j < je) {
+        zrow[j] = zold;
+        if constexpr (NDX) {
+#pragma unroll
+          for (int e = 0; e < DIM; ++e) xrow[j * DIM + e] = first ? xv[e] : xrow[j * DIM + e] + xv[e];
+        }
+      }
+      if constexpr (NC > 0) {
+        if ((t + 1) % (kFlush / TILE) == 0 || t + 1 == ntiles) flush();  // own row of zred only
+      }
+    }
+    if constexpr (NC > 0) {
+      // lanes 8 i .. 8 i + 7 hold sum 8 k + i: query r = 8 h + i of component c at k = (c R + 8 h) / 8
+#pragma unroll
+      for (int h = 0; h < R / 8; ++h) {
+        const int64_t i = qw + 8 * h + lane / 8;
+        double v[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+          double t;
+          if constexpr (LSUM)
+            t = lsum[wave][(c * R) / 8 + h][lane];
+          else
+            t = sums[(c * R) / 8 + h];
+#pragma unroll
+          for (int x = 1; x < 8; x <<= 1) t += shfl_xor64(t, x);
+          if constexpr (EXCL) t += static_cast<double>(__shfl(own[c], 8 * h + lane / 8));
+          v[NDP ? c : c + 1] = t;
+        }
+        if ((lane & 7) == 0 && i < m) {
+          const double4 o = make_double4(v[0], v[1], v[2], v[3]);
+          part_q[static_cast<int64_t>(blockIdx.y) * m + i] = o;
+        }
+      }
+    }
+  }
+  // A group without any query block still owns a partial row: make it zero.
+  if (first) {
+    for (int64_t j = jb + tid; j < je; j += NT) {
+      zrow[j] = 0.0;
+      if constexpr (NDX) {
+#pragma unroll
+        for (int e = 0; e < DIM; ++e) xrow[j * DIM + e] = 0.0;
+      }
+    }
+  }
+}
+
 template <typename T, int DIM, int L, int PM, bool REL = false>
 hipError_t launch_bwd_fused_t(const BwdArgs& a, int groups, int ranges, int64_t chunk, hipStream_t st) {
   const bool ndp = (a.flags & 0x4u) != 0, ndq = (a.flags & 0x8u) != 0, ndx = a.part_x != nullptr;
@@ -342,11 +741,21 @@ hipError_t launch_bwd_fused_t(const BwdArgs& a, int groups, int ranges, int64_t 
   const T nhp = static_cast<T>(-0.5 * a.p);
   const T* sz = static_cast<const T*>(a.saved_z);
   const T* go = static_cast<const T*>(a.grad_out);
-  constexpr int NT = FusedShape<T>::NT;
+#define IDW_BF_ARGS                                                                                       \
+  a.data, a.n, a.query, a.m, chunk, groups, nhp, a.flags, a.hdr, sz, go, a.saved_den, a.part_q, a.part_z, \
+      a.part_x, a.route
 #define IDW_BF(DP, DQ, DX)                                                                                  \
-  hipLaunchKernelGGL((k_bwd_fused<T, DIM, L, PM, 2, DP, DQ, DX, REL>), grid, dim3(NT), 0, st, a.data, a.n,    \
-                     a.query, a.m, chunk, groups, nhp, a.flags, a.hdr, sz, go, a.saved_den, a.part_q, a.part_z, \
-                     a.part_x, a.route, a.p)
+  do {                                                                                                      \
+    if constexpr (sizeof(T) == 8)                                                                           \
+      hipLaunchKernelGGL((k_bwd_fused<T, DIM, L, PM, 2, DP, DQ, DX>), grid, dim3(kFNT64), 0, st,            \
+                         IDW_BF_ARGS);                                                                      \
+    else if (a.flags & 1u)                                                                                  \
+      hipLaunchKernelGGL((k_bwd_fused32<DIM, L, PM, DP, DQ, DX, REL, true>), grid, dim3(64 * kFusedWaves),  \
+                         0, st, IDW_BF_ARGS, a.p);                                                          \
+    else                                                                                                    \
+      hipLaunchKernelGGL((k_bwd_fused32<DIM, L, PM, DP, DQ, DX, REL, false>), grid, dim3(64 * kFusedWaves), \
+                         0, st, IDW_BF_ARGS, a.p);                                                          \
+  } while (0)
   // The data-coordinate gradient is instantiated with both query-direction sums (they share
   // its per-pair factors); merges write only what was requested.  With relative weights
   // every request runs here, dz alone included.
@@ -363,6 +772,7 @@ hipError_t launch_bwd_fused_t(const BwdArgs& a, int groups, int ranges, int64_t 
   else
     return hipErrorInvalidValue;
 #undef IDW_BF
+#undef IDW_BF_ARGS
   return hipGetLastError();
 }
 
