@@ -187,20 +187,28 @@ constexpr int64_t kPartBudget = int64_t(1) << 31;
 // chunks, 102 us with 20; 32,768^2 FP32: 268 -> 250 us), while from 65,536^2 on the longer
 // merge of finer splits outweighs the fuller grid (65,536^2: 789 us with 32 chunks, 803
 // with 128), so the smaller minimum applies only to the small grids.
+// The forward (`fine`) goes down to chunks of one 64-record block where even 1-tile chunks
+// would leave fewer than 512 workgroups (1,024 points x 1,000 queries, FP32: the sweep 20.4 us
+// in 2 chunks, 5.3 us in 16; 10,240^2 FP64: 59.5 us in 20 chunks, 52.8 us in 80).
 static void choose_split(int64_t len, int64_t blocks, int want_split, int64_t unit, int64_t other, int& split,
-                         int64_t& chunk) {
+                         int64_t& chunk, bool fine = false) {
   int64_t s = want_split;
+  int64_t grain = kTile;
   if (s <= 0) {
     const int64_t target = 16384;
     const int64_t b = blocks > 0 ? blocks : 1;
     s = cdiv(target, b);
     const int64_t s4 = cdiv(len, 4 * kTile);
     s = std::min<int64_t>(s, b * s4 < 2048 ? cdiv(len, kTile) : s4);
+    if (fine && b * cdiv(len, kTile) < 512) {
+      grain = 64;
+      s = std::min<int64_t>(cdiv(len, grain), cdiv(1024, b));
+    }
     s = std::min<int64_t>(s, std::max<int64_t>(1, kPartBudget / (unit * std::max<int64_t>(other, 1))));
   }
   if (s < 1) s = 1;
   if (s > 1024) s = 1024;
-  chunk = cdiv(cdiv(len, s), kTile) * kTile;
+  chunk = cdiv(cdiv(len, s), grain) * grain;
   split = static_cast<int>(cdiv(len, chunk));
 }
 
@@ -211,7 +219,7 @@ WsPlan plan_workspace(const idw_points* data, const idw_points* query, int preci
   const int64_t n = data->n, m = query->n;
   // forward
   w.qf = (cfg && cfg->queries_per_lane) ? cfg->queries_per_lane : 4;
-  choose_split(n, cdiv(m, kWG * w.qf), cfg ? cfg->split : 0, sizeof(double2), m, w.split_f, w.chunk_f);
+  choose_split(n, cdiv(m, kWG * w.qf), cfg ? cfg->split : 0, sizeof(double2), m, w.split_f, w.chunk_f, true);
   // backward: query sweep over data chunks, data sweep over query chunks
   w.qq = 2;
   choose_split(n, cdiv(m, kWG * w.qq), 0, sizeof(double4), m, w.split_q, w.chunk_q);
@@ -299,7 +307,7 @@ WsPlan plan_workspace(const idw_points* data, const idw_points* query, int preci
 struct LayoutFns {
   hipError_t (*fwd_sweep)(const FwdArgs&, bool, hipStream_t);
   hipError_t (*fwd_fixup)(const FwdArgs&, bool, hipStream_t);
-  hipError_t (*bbox)(const DevPts&, int64_t, int, bool, double*, int, hipStream_t);
+  hipError_t (*header)(const HeaderArgs&, int, bool, hipStream_t);
   hipError_t (*bwd_query)(const BwdArgs&, bool, hipStream_t);
   hipError_t (*bwd_data)(const BwdArgs&, bool, hipStream_t);
   hipError_t (*bwd_datax)(const BwdArgs&, bool, hipStream_t);
@@ -310,7 +318,7 @@ struct LayoutFns {
 };
 
 #define IDW_FNS(NAME)                                                                   \
-  {fwd_sweep_##NAME, fwd_fixup_##NAME, bbox_##NAME,      bwd_query_##NAME, bwd_data_##NAME, \
+  {fwd_sweep_##NAME, fwd_fixup_##NAME, header_##NAME,    bwd_query_##NAME, bwd_data_##NAME, \
    bwd_datax_##NAME, bwd_fixup_##NAME, bwd_fused_##NAME, near_check_##NAME, grid_##NAME}
 static const LayoutFns kFns[5] = {IDW_FNS(soa), IDW_FNS(aos), IDW_FNS(aoas), IDW_FNS(hybrid), IDW_FNS(soaos)};
 #undef IDW_FNS
@@ -358,11 +366,27 @@ int check_workspace(void* ws, size_t bytes, size_t need) {
 // FP32 sweeps).
 hipError_t enqueue_header(const idw_points* data, double p, bool f64, bool rel, char* ws, const WsPlan& w,
                           hipStream_t st) {
-  hipError_t e = fns(data->layout).bbox(dev_pts(data), data->n, data->dim, f64,
-                                        reinterpret_cast<double*>(ws + w.bbox), w.nbbox, st);
-  if (e != hipSuccess) return e;
-  return bbox_final(reinterpret_cast<double*>(ws + w.bbox), w.nbbox, data->dim, p, !f64, rel,
-                    reinterpret_cast<double*>(ws + w.hdr), st);
+  HeaderArgs h;
+  h.data = dev_pts(data);
+  h.n = data->n;
+  h.p = p;
+  h.rel = rel;
+  h.part = reinterpret_cast<double*>(ws + w.bbox);
+  h.nblocks = w.nbbox;
+  h.hdr = reinterpret_cast<double*>(ws + w.hdr);
+  return fns(data->layout).header(h, data->dim, f64, st);
+}
+
+static RouteArgs route_args(int64_t m, char* ws, const WsPlan& w) {
+  RouteArgs r;
+  r.m = m;
+  r.hdr = reinterpret_cast<const double*>(ws + w.hdr);
+  r.hint = reinterpret_cast<int*>(ws + w.hdr + 256);
+  r.route = reinterpret_cast<uint8_t*>(ws + w.flag);
+  r.list = reinterpret_cast<int*>(ws + w.list);
+  r.bcnt = reinterpret_cast<int*>(ws + w.bcnt);
+  r.minb = reinterpret_cast<unsigned long long*>(ws + w.near_min);
+  return r;
 }
 
 static GridArgs grid_args(const idw_points* data, const idw_points* query, bool f64, bool excl, char* ws,
@@ -388,13 +412,6 @@ static GridArgs grid_args(const idw_points* data, const idw_points* query, bool 
   return g;
 }
 
-// Builds the grid when its gate (set by grid_setup) is open: counts, scan, scatter.
-static hipError_t grid_build(const LayoutFns& F, const GridArgs& g, hipStream_t st) {
-  hipError_t e = fill_zero(g.cnt, sizeof(int) * static_cast<size_t>(g.ncell_max + 1), st);
-  if (e != hipSuccess) return e;
-  return F.grid(g, true, st);
-}
-
 static NearArgs near_args(const idw_points* data, const idw_points* query, bool f64, bool excl, char* ws,
                           const WsPlan& w) {
   NearArgs na;
@@ -406,7 +423,6 @@ static NearArgs near_args(const idw_points* data, const idw_points* query, bool 
   na.f64 = f64;
   na.excl = excl;
   na.hdr = reinterpret_cast<const double*>(ws + w.hdr);
-  na.route = reinterpret_cast<uint8_t*>(ws + w.flag);
   na.minb = reinterpret_cast<unsigned long long*>(ws + w.near_min);
   return na;
 }
@@ -418,6 +434,7 @@ static NearArgs near_args(const idw_points* data, const idw_points* query, bool 
 static hipError_t nearest_all(const LayoutFns& F, const idw_points* data, const idw_points* query, bool excl,
                               char* ws, const WsPlan& w, hipStream_t st) {
   NearArgs na = near_args(data, query, false, excl, ws, w);
+  na.init = true;
   if (!w.grid_on) {
     na.all = true;
     return F.near_check(na, st);
@@ -425,8 +442,8 @@ static hipError_t nearest_all(const LayoutFns& F, const idw_points* data, const 
   GridArgs g = grid_args(data, query, false, excl, ws, w);
   g.nearest = true;
   g.hint += kGridNearestSlots;  // its own gate and counters: the candidate check comes later
-  hipError_t e = grid_setup(g, 1, true, st);
-  if (e == hipSuccess) e = grid_build(F, g, st);
+  hipError_t e = grid_setup(g, 1, nullptr, st);
+  if (e == hipSuccess) e = F.grid(g, true, st);
   if (e == hipSuccess) e = F.grid(g, false, st);
   if (e != hipSuccess) return e;
   na.list = g.blist;  // the queries the ring search handed back
@@ -435,35 +452,29 @@ static hipError_t nearest_all(const LayoutFns& F, const idw_points* data, const 
 }
 
 // Settles the route of every query after a sweep (or from the saved denominators): the
-// candidates are compacted and checked for a data point within 1e-6 of the extent, then the
-// queries routed to FP64 are compacted into the list the fix-ups read.
+// candidates, already collected, are checked for a data point within 1e-6 of the extent, then
+// the queries routed to FP64 are listed for the fix-ups.
 static hipError_t settle_routes(const LayoutFns& F, const idw_points* data, const idw_points* query,
                                 bool f64, bool excl, char* ws, const WsPlan& w, hipStream_t st) {
-  uint8_t* route = reinterpret_cast<uint8_t*>(ws + w.flag);
-  int* bcnt = reinterpret_cast<int*>(ws + w.bcnt);
-  int* list = reinterpret_cast<int*>(ws + w.list);
-  int* count = reinterpret_cast<int*>(ws + w.hdr + 256);
-  const int64_t m = query->n;
-  hipError_t e = compact_flags(route, m, bcnt, list, count, F_CANDIDATE, st);
-  if (e != hipSuccess) return e;
+  const RouteArgs r = route_args(query->n, ws, w);
+  hipError_t e;
   NearArgs na = near_args(data, query, f64, excl, ws, w);
-  na.list = list;
-  na.count = count;
-  if (w.grid_on) {
-    // Many candidates: the grid's fixed-radius check, then the brute-force kernels for the
-    // candidates it hands back; few: the brute-force kernels for all of them.
+  na.list = r.list;
+  na.count = r.hint + kCandSlot;
+  if (w.grid_on && query->n >= kGridMinCand) {
+    // Many candidates: the grid's fixed-radius check, then the brute-force kernel for the
+    // candidates it hands back; few: the brute-force kernel for all of them.
     GridArgs g = grid_args(data, query, f64, excl, ws, w);
-    g.list = list;
-    if ((e = grid_setup(g, 0, true, st)) != hipSuccess) return e;
-    na.count = g.hint + GI_BRUTE;
-    if ((e = F.near_check(na, st)) != hipSuccess) return e;
-    if ((e = grid_build(F, g, st)) != hipSuccess) return e;
+    g.list = r.list;
+    if ((e = grid_setup(g, 0, r.hint + kCandSlot, st)) != hipSuccess) return e;
+    if ((e = F.grid(g, true, st)) != hipSuccess) return e;
     if ((e = F.grid(g, false, st)) != hipSuccess) return e;
-    na.list = g.blist;
-    na.count = g.hint + GI_FALLBACK;
+    na.count = g.hint + GI_BRUTE;
+    na.list2 = g.blist;
+    na.count2 = g.hint + GI_FALLBACK;
   }
   if ((e = F.near_check(na, st)) != hipSuccess) return e;
-  return compact_flags(route, m, bcnt, list, count, F_FP64, st);
+  return settle(r, f64, st);
 }
 
 // ---- optional event timing of the sweep kernels ----
@@ -661,9 +672,7 @@ static int forward_impl(const idw_points* data, const idw_points* query, double 
     return rc;
   if ((rc = check_hip(timed(IDW_T_FWD_SWEEP, st, [&] { return F.fwd_sweep(a, f64, st); }), "forward sweep")))
     return rc;
-  if (a.split > 1 &&
-      (rc = check_hip(merge_split(a.part, m, a.split, a.hdr, out_z, f64, out_den, a.flag, st), "merge")))
-    return rc;
+  if ((rc = check_hip(merge_split(a, route_args(m, ws, w), f64, st), "merge"))) return rc;
   if ((rc = check_hip(settle_routes(F, data, query, f64, excl, ws, w, st), "near-coincidence check")))
     return rc;
   if ((rc = check_hip(F.fwd_fixup(a, f64, st), "FP64 fix-up"))) return rc;
@@ -765,7 +774,7 @@ int idw_backward(const idw_points* data, const idw_points* query, double p, int3
   const bool rel = !f64 && p >= kRelP && !separate && w.fused_groups > 0;
   a.rel = rel;
   if ((rc = check_hip(enqueue_header(data, p, f64, rel, ws, w, st), "extent kernels"))) return rc;
-  if ((rc = check_hip(flags_from_den(saved_den, m, a.hdr, flag, st), "flags"))) return rc;
+  if ((rc = check_hip(flags_from_den(saved_den, route_args(m, ws, w), f64, st), "flags"))) return rc;
   if ((rc = check_hip(settle_routes(F, data, query, f64, (flags & IDW_EXCLUDE_SELF) != 0, ws, w, st),
                       "near-coincidence check")))
     return rc;
@@ -782,25 +791,20 @@ int idw_backward(const idw_points* data, const idw_points* query, double p, int3
     BwdArgs b = a;
     b.split_q = w.fused_ranges;
     b.split_z = w.fused_groups;
-    if ((ndp || ndq) && (rc = check_hip(bwd_qmerge(b, f64, st), "query merge"))) return rc;
-    if (ndz && (rc = check_hip(bwd_zmerge(b, f64, st), "data merge"))) return rc;
-    if (ndx && (rc = check_hip(bwd_xmerge(b, w.fused_groups, f64, st), "data-coordinate merge"))) return rc;
+    if ((rc = check_hip(bwd_merge(b, ndp || ndq, ndz, ndx, f64, st), "merge"))) return rc;
   } else {
     if (ndp || ndq) {
       if ((rc = check_hip(timed(IDW_T_BWD_QUERY, st, [&] { return F.bwd_query(a, f64, st); }), "query sweep")))
         return rc;
-      if ((rc = check_hip(bwd_qmerge(a, f64, st), "query merge"))) return rc;
     }
     if (ndx) {  // one data-direction sweep yields dz and dx
       if ((rc = check_hip(timed(IDW_T_BWD_DATA, st, [&] { return F.bwd_datax(a, f64, st); }), "data sweep")))
         return rc;
-      if (ndz && (rc = check_hip(bwd_zmerge(a, f64, st), "data merge"))) return rc;
-      if ((rc = check_hip(bwd_xmerge(a, w.split_z, f64, st), "data-coordinate merge"))) return rc;
     } else if (ndz) {
       if ((rc = check_hip(timed(IDW_T_BWD_DATA, st, [&] { return F.bwd_data(a, f64, st); }), "data sweep")))
         return rc;
-      if ((rc = check_hip(bwd_zmerge(a, f64, st), "data merge"))) return rc;
     }
+    if ((rc = check_hip(bwd_merge(a, ndp || ndq, ndz, ndx, f64, st), "merge"))) return rc;
   }
   if ((rc = check_hip(F.bwd_fixup(a, f64, st), "FP64 fix-up"))) return rc;
   if (ndp && (rc = check_hip(dp_final(a.wg_dp, w.nwg_dp, a.slot_dp, a.count, grad_p, st), "dp reduction")))

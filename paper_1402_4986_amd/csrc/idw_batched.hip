@@ -270,7 +270,7 @@ __device__ __forceinline__ void kb_item(const BInst& I, const BItem& it, const d
   __syncthreads();
   for (int t = 0; t < ntiles; ++t) {
     if (t + 1 < ntiles) fetch(t + 1);
-    fwd_tile_run<DIM, PM, kBQ, false, REL>(tile[t & 1], qc, I.nhp, sg, nacc, dacc);
+    fwd_tile_run<DIM, PM, kBQ, false, REL>(tile[t & 1], kTile, qc, I.nhp, sg, nacc, dacc);
     if (t + 1 < ntiles) put((t + 1) & 1);
     __syncthreads();
   }

@@ -294,16 +294,13 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(WPE, 8))) v
 
 // Merges query-sweep partials: dq_i for unflagged queries, dp partial per workgroup.
 template <typename T, int DIM>
-__global__ __launch_bounds__(kWG) void k_bwd_qmerge(const double4* __restrict__ part, int64_t m,
-                                                    int split, double p,
-                                                    const double* __restrict__ hdr,
-                                                    const T* __restrict__ grad_out,
-                                                    const double* __restrict__ saved_den,
-                                                    T* __restrict__ grad_q,
-                                                    double* __restrict__ wg_dp,
-                                                    const uint8_t* __restrict__ route) {
+__device__ __forceinline__ void bwd_qmerge_block(int64_t block, const double4* __restrict__ part, int64_t m,
+                                                 int split, double p, const double* __restrict__ hdr,
+                                                 const T* __restrict__ grad_out,
+                                                 const double* __restrict__ saved_den, T* __restrict__ grad_q,
+                                                 double* __restrict__ wg_dp, const uint8_t* __restrict__ route) {
   __shared__ double red[kWG];
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * kWG + threadIdx.x;
+  const int64_t i = block * kWG + threadIdx.x;
   double dpi = 0.0;
   if (i < m) {
     const double D = saved_den[i];
@@ -337,8 +334,9 @@ __global__ __launch_bounds__(kWG) void k_bwd_qmerge(const double4* __restrict__ 
       }
     }
   }
+  if (!wg_dp) return;
   const double tot = block_sum(dpi, red);
-  if (threadIdx.x == 0 && wg_dp) wg_dp[blockIdx.x] = tot;
+  if (threadIdx.x == 0) wg_dp[block] = tot;
 }
 
 // One LDS tile of the data sweep: for the lane's Q data points, accumulate a_i * w_ij.
@@ -458,9 +456,9 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(WPE, 8))) v
 }
 
 template <typename T>
-__global__ __launch_bounds__(kWG) void k_bwd_zmerge(const double* __restrict__ part, int64_t n,
-                                                    int split, T* __restrict__ grad_z) {
-  const int64_t j = static_cast<int64_t>(blockIdx.x) * kWG + threadIdx.x;
+__device__ __forceinline__ void bwd_zmerge_block(int64_t block, const double* __restrict__ part, int64_t n,
+                                                 int split, T* __restrict__ grad_z) {
+  const int64_t j = block * kWG + threadIdx.x;
   if (j >= n) return;
   double h = 0.0, l = 0.0;
   for (int c = 0; c < split; ++c) two_sum_acc(h, l, part[static_cast<int64_t>(c) * n + j]);
@@ -628,15 +626,33 @@ __global__ __launch_bounds__(kWG) void k_bwd_datax(DevPts data, int64_t n, DevPt
 // Merges data-coordinate partials in chunk order: dx_j = p s sum_c X_j (s: the sweep's
 // coordinate scale, which converts the scaled sums back to caller units).
 template <typename T, int DIM>
-__global__ __launch_bounds__(kWG) void k_bwd_xmerge(const double* __restrict__ part, int64_t n,
-                                                    int split, double p,
-                                                    const double* __restrict__ hdr,
-                                                    T* __restrict__ grad_x) {
-  const int64_t t = static_cast<int64_t>(blockIdx.x) * kWG + threadIdx.x;
+__device__ __forceinline__ void bwd_xmerge_block(int64_t block, const double* __restrict__ part, int64_t n,
+                                                 int split, double p, const double* __restrict__ hdr,
+                                                 T* __restrict__ grad_x) {
+  const int64_t t = block * kWG + threadIdx.x;
   if (t >= n * DIM) return;
   double h = 0.0, l = 0.0;
   for (int c = 0; c < split; ++c) two_sum_acc(h, l, part[static_cast<int64_t>(c) * n * DIM + t]);
   grad_x[t] = static_cast<T>(p * hdr[H_SCALE] * (h + l));
+}
+
+// The merges of one adjoint call in one launch: the first nq workgroups merge queries, the next
+// nz data values, the rest data coordinates (none where a gradient was not requested).
+template <typename T, int DIM>
+__global__ __launch_bounds__(kWG) void k_bwd_merge(unsigned nq, unsigned nz, const double4* __restrict__ part_q,
+                                                   int64_t m, int split_q, double p,
+                                                   const double* __restrict__ hdr, const T* __restrict__ grad_out,
+                                                   const double* __restrict__ saved_den, T* __restrict__ grad_q,
+                                                   double* __restrict__ wg_dp, const uint8_t* __restrict__ route,
+                                                   const double* __restrict__ part_z, int64_t n, int split_z,
+                                                   T* __restrict__ grad_z, const double* __restrict__ part_x,
+                                                   T* __restrict__ grad_x) {
+  if (blockIdx.x < nq)
+    bwd_qmerge_block<T, DIM>(blockIdx.x, part_q, m, split_q, p, hdr, grad_out, saved_den, grad_q, wg_dp, route);
+  else if (blockIdx.x < nq + nz)
+    bwd_zmerge_block<T>(blockIdx.x - nq, part_z, n, split_z, grad_z);
+  else
+    bwd_xmerge_block<T, DIM>(blockIdx.x - nq - nz, part_x, n, split_z, p, hdr, grad_x);
 }
 
 // FP64 fix-up of the adjoint for flagged queries (exact hits and near-coincident points),
@@ -1039,26 +1055,19 @@ hipError_t bwd_fix_pm(const BwdArgs& a, hipStream_t st) {
 }
 
 template <typename T, int DIM>
-hipError_t launch_bwd_qmerge(const BwdArgs& a, int split, const double4* part, hipStream_t st) {
-  dim3 grid(static_cast<unsigned>((a.m + kWG - 1) / kWG));
-  hipLaunchKernelGGL((k_bwd_qmerge<T, DIM>), grid, dim3(kWG), 0, st, part, a.m, split, a.p, a.hdr,
-                     static_cast<const T*>(a.grad_out), a.saved_den, static_cast<T*>(a.grad_q),
-                     a.wg_dp, a.route);
-  return hipGetLastError();
-}
-
-template <typename T>
-hipError_t launch_bwd_zmerge(const BwdArgs& a, int split, const double* part, hipStream_t st) {
-  dim3 grid(static_cast<unsigned>((a.n + kWG - 1) / kWG));
-  hipLaunchKernelGGL((k_bwd_zmerge<T>), grid, dim3(kWG), 0, st, part, a.n, split,
-                     static_cast<T*>(a.grad_z));
-  return hipGetLastError();
-}
-
-template <typename T, int DIM>
-hipError_t launch_bwd_xmerge(const BwdArgs& a, int split, hipStream_t st) {
-  dim3 grid(static_cast<unsigned>((a.n * DIM + kWG - 1) / kWG));
-  hipLaunchKernelGGL((k_bwd_xmerge<T, DIM>), grid, dim3(kWG), 0, st, a.part_x, a.n, split, a.p, a.hdr,
+hipError_t launch_bwd_merge(const BwdArgs& a, bool query, bool data, bool x, hipStream_t st) {
+  auto blocks = [](bool on, int64_t len) { return on ? static_cast<unsigned>((len + kWG - 1) / kWG) : 0u; };
+  const unsigned nq = blocks(query, a.m), nz = blocks(data, a.n), nx = blocks(x, a.n * DIM);
+  if (nq + nz + nx == 0) return hipSuccess;
+  if (nq + nz + nx > 0xffffffu && (nq != 0) + (nz != 0) + (nx != 0) > 1) {
+    // a launch takes fewer than 2^32 threads: the largest sets are merged one by one
+    hipError_t e = launch_bwd_merge<T, DIM>(a, query, false, false, st);
+    if (e == hipSuccess) e = launch_bwd_merge<T, DIM>(a, false, data, false, st);
+    return e == hipSuccess ? launch_bwd_merge<T, DIM>(a, false, false, x, st) : e;
+  }
+  hipLaunchKernelGGL((k_bwd_merge<T, DIM>), dim3(nq + nz + nx), dim3(kWG), 0, st, nq, nz, a.part_q, a.m, a.split_q,
+                     a.p, a.hdr, static_cast<const T*>(a.grad_out), a.saved_den, static_cast<T*>(a.grad_q), a.wg_dp,
+                     a.route, a.part_z, a.n, a.split_z, static_cast<T*>(a.grad_z), a.part_x,
                      static_cast<T*>(a.grad_x));
   return hipGetLastError();
 }

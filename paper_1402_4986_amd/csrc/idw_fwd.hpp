@@ -25,6 +25,9 @@ namespace idw {
 __device__ __forceinline__ float fmaT(float a, float b, float c) { return fmaf(a, b, c); }
 __device__ __forceinline__ double fmaT(double a, double b, double c) { return fma(a, b, c); }
 
+__device__ __forceinline__ float maxT(float a, float b) { return fmaxf(a, b); }
+__device__ __forceinline__ double maxT(double a, double b) { return fmax(a, b); }
+
 template <typename T>
 __device__ __forceinline__ T infT() {
   return __builtin_huge_valf();
@@ -85,19 +88,19 @@ struct KahanSum {
 // accumulator and pair; the accuracy variant).
 // REL = true: relative weights, the squared distance multiplied by the query's sigma
 // before the weight is taken (one more multiply per pair).
-// TAIL = true: only the first `cnt` records of the tile are data (the chunk's last tile);
-// the padding records after them are never visited, so that no weight of theirs, however
-// small, reaches the denominator.
+// Records [begin, end) of the tile, begin a multiple of 64: a full tile (FULL), whole 64-record
+// blocks, or with TAIL a last block of fewer.  Padding records are never visited, so that no
+// weight of theirs, however small, reaches the denominator.
 template <typename T, int DIM, int PM, int Q, bool DIAG, int UNR, bool KH = false, bool REL = false,
-          bool TAIL = false, typename Acc>
-__device__ __forceinline__ void fwd_tile(const RecTile<T, DIM, kTile>& tl, int64_t jt, int cnt,
+          bool TAIL = false, bool FULL = false, typename Acc>
+__device__ __forceinline__ void fwd_tile(const RecTile<T, DIM, kTile>& tl, int64_t jt, int begin, int end,
                                          const T (&qc)[Q][3], const int64_t (&qi)[Q], T nhp,
                                          const T (&sg)[Q], Acc (&num)[Q], Acc (&den)[Q]) {
   constexpr int CH = 64;
-  const int lim = TAIL ? cnt : kTile;
+  const int lim = FULL ? kTile : end;
   if constexpr (KH) {
 #pragma unroll UNR
-    for (int jj = 0; jj < lim; ++jj) {
+    for (int jj = begin; jj < lim; ++jj) {
       const P4<T> d = tl.get(jj);
       const T dv = (DIM == 3) ? d.w : d.z;
 #pragma unroll
@@ -147,15 +150,15 @@ __device__ __forceinline__ void fwd_tile(const RecTile<T, DIM, kTile>& tl, int64
   // FP64 general p goes block by block; unrolled over the tile, the compiler keeps every
   // 64-record block's partial sums live until the tile's end, which differs by at most 2%
   // either way for the other FP64 weights.
-  if constexpr (PM == PM_GEN || sizeof(T) == 4) {
+  if constexpr (PM == PM_GEN || !FULL) {
 #pragma unroll 1
-    for (int c0 = 0; c0 < lim; c0 += CH) block(c0);
+    for (int c0 = begin; c0 < lim; c0 += CH) block(c0);
   } else {
     for (int c0 = 0; c0 < lim; c0 += CH) block(c0);
   }
 }
 
-// A full tile in FP32 without a self pair: groups of 4 records, whose 4 Q weights form one
+// Whole 64-record blocks [0, end) in FP32 without a self pair: groups of 4 records, whose 4 Q weights form one
 // run of transcendentals (idw_phase.hpp).  The same operations in the same order per query
 // as fwd_tile, so the same bits.  Bound by instruction issue: 6 plain instructions and a
 // reciprocal per pair at p = 2, 20.6 cycles with the waves in step.  Against records read one
@@ -164,11 +167,11 @@ __device__ __forceinline__ void fwd_tile(const RecTile<T, DIM, kTile>& tl, int64
 // 102,400 x 99,991, 3.95 -> 2.75 ms; the 64 batched instances 58.7 -> 45.0 ms.  Unrolled over
 // the whole 64-record block instead of 4 groups: within 0.3% in 2-D, 2-4% slower in 3-D.
 template <int DIM, int PM, int Q, bool KH, bool REL, typename Acc>
-__device__ __forceinline__ void fwd_tile_run(const RecTile<float, DIM, kTile>& tl, const float (&qc)[Q][3],
-                                             float nhp, const float (&sg)[Q], Acc (&num)[Q], Acc (&den)[Q]) {
+__device__ __forceinline__ void fwd_tile_run(const RecTile<float, DIM, kTile>& tl, int end,
+                                             const float (&qc)[Q][3], float nhp, const float (&sg)[Q], Acc (&num)[Q], Acc (&den)[Q]) {
   constexpr int CH = 64, G = 4;
 #pragma unroll 1
-  for (int c0 = 0; c0 < kTile; c0 += CH) {
+  for (int c0 = 0; c0 < end; c0 += CH) {
     float an[Q], ad[Q];
 #pragma unroll
     for (int k = 0; k < Q; ++k) an[k] = ad[k] = 0.f;
@@ -310,17 +313,20 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(Tune::WMIN,
     const int64_t jt = jb + static_cast<int64_t>(t) * kTile;
     const int cnt = static_cast<int>((je - jt) < kTile ? (je - jt) : kTile);
     const bool diag = excl && jt < q0 + kWG * Q && q0 < jt + kTile;
-    if (cnt < kTile) {
-      if (diag)
-        fwd_tile<T, DIM, PM, Q, true, 1, KH, REL, true>(tile[t & 1], jt, cnt, qc, qi, nhp, sg, nacc, dacc);
-      else
-        fwd_tile<T, DIM, PM, Q, false, 1, KH, REL, true>(tile[t & 1], jt, cnt, qc, qi, nhp, sg, nacc, dacc);
-    } else if (diag) {
-      fwd_tile<T, DIM, PM, Q, true, 1, KH, REL>(tile[t & 1], jt, kTile, qc, qi, nhp, sg, nacc, dacc);
-    } else if constexpr (sizeof(T) == 4) {
-      fwd_tile_run<DIM, PM, Q, KH, REL>(tile[t & 1], qc, nhp, sg, nacc, dacc);
+    const auto& tl = tile[t & 1];
+    if (diag) {
+      fwd_tile<T, DIM, PM, Q, true, 1, KH, REL, true>(tl, jt, 0, cnt, qc, qi, nhp, sg, nacc, dacc);
     } else {
-      fwd_tile<T, DIM, PM, Q, false, Tune::UNR, KH, REL>(tile[t & 1], jt, kTile, qc, qi, nhp, sg, nacc, dacc);
+      const int whole = cnt & ~63;
+      if constexpr (sizeof(T) == 4) {
+        fwd_tile_run<DIM, PM, Q, KH, REL>(tl, whole, qc, nhp, sg, nacc, dacc);
+      } else if (whole == kTile) {
+        fwd_tile<T, DIM, PM, Q, false, Tune::UNR, KH, REL, false, true>(tl, jt, 0, kTile, qc, qi, nhp, sg, nacc, dacc);
+      } else if (whole > 0) {
+        fwd_tile<T, DIM, PM, Q, false, Tune::UNR, KH, REL>(tl, jt, 0, whole, qc, qi, nhp, sg, nacc, dacc);
+      }
+      if (whole < cnt)
+        fwd_tile<T, DIM, PM, Q, false, 1, KH, REL, true>(tl, jt, whole, cnt, qc, qi, nhp, sg, nacc, dacc);
     }
     if (t + 1 < ntiles) put((t + 1) & 1);
     __syncthreads();
@@ -343,9 +349,8 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(Tune::WMIN,
   }
 }
 
-// Nearest-distance check of the candidate queries (route F_CANDIDATE, compacted in `list`,
-// *count of them), in three kernels:
-//  k_near_init   sets each candidate's minimum to +inf;
+// Nearest-distance check of the candidate queries (route F_CANDIDATE, collected in a list by
+// append_candidates, which also sets their minima to +inf):
 //  k_near_check  takes work items (block of kWG * Q candidates, data chunk) in turn: the
 //                data chunk goes through LDS tiles as in the forward sweep, each query keeps
 //                its smallest squared distance in scaled units (the leave-one-out self pair
@@ -353,9 +358,10 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(Tune::WMIN,
 //                bits of the non-negative value (order-independent, so deterministic).  The
 //                data range is cut into as many chunks as keep about kNearGrid workgroups
 //                busy when the candidates are few, none when they fill the grid;
-//  k_near_finish gives a candidate with a data point closer than 1e-6 of the extent
-//                F_FP64, the others F_FP32 (their sweep results stand).
-// 5 VALU operations per pair (2 sub, mul + fma, min).
+//  settle_route  (the settling kernels) gives a candidate with a data point closer than 1e-6
+//                of the extent F_FP64, the others F_FP32 (their sweep results stand).
+// 5 VALU operations per pair (2 sub, mul + fma, min).  k_near_init sets minima to +inf where
+// every query, or a list of them, needs its nearest distance.
 constexpr int kNearGrid = 1024;      // workgroups of the nearest-distance check
 // Fewest data points per chunk: one tile.  A few candidates (the common case from p = 2 on)
 // make one block, whose time is that of its chunk (131,072 or 1M points: 480 us with chunks of
@@ -388,27 +394,27 @@ __global__ __launch_bounds__(kWG) void k_near_init(const int* __restrict__ list,
     minb[list ? list[i] : i] = min_bits(infT<T>());
 }
 
+// Route of a query after the nearest-distance check.
 template <typename T>
-__global__ __launch_bounds__(kWG) void k_near_finish(const int* __restrict__ list, const int* __restrict__ count,
-                                                     const unsigned long long* __restrict__ minb,
-                                                     const double* __restrict__ hdr, uint8_t* __restrict__ route) {
-  const int cnt = *count;
-  const T near = static_cast<T>(hdr[H_NEAR_R2]);
-  for (int64_t i = static_cast<int64_t>(blockIdx.x) * kWG + threadIdx.x; i < cnt;
-       i += static_cast<int64_t>(gridDim.x) * kWG) {
-    const int q = list[i];
-    route[q] = from_min_bits<T>(minb[q]) < near ? F_FP64 : F_FP32;
-  }
+__device__ __forceinline__ uint8_t settle_route(uint8_t r, unsigned long long minb, const double* __restrict__ hdr) {
+  if (r != F_CANDIDATE) return r;
+  return from_min_bits<T>(minb) < static_cast<T>(hdr[H_NEAR_R2]) ? F_FP64 : F_FP32;
 }
 
 template <typename T, int DIM, int L, int Q, bool EXCL>
 __global__ __launch_bounds__(kWG) void k_near_check(DevPts data, int64_t n, DevPts query,
                                                     const int* __restrict__ list,
-                                                    const int* __restrict__ count, int64_t mall,
+                                                    const int* __restrict__ count,
+                                                    const int* __restrict__ list2,
+                                                    const int* __restrict__ count2, int64_t mall,
                                                     const double* __restrict__ hdr,
                                                     unsigned long long* __restrict__ minb) {
   __shared__ P4<T> tile[2][kTile];
-  const int64_t cnt = list ? static_cast<int64_t>(*count) : mall;
+  int64_t cnt = list ? static_cast<int64_t>(*count) : mall;
+  if (cnt == 0 && list2) {  // a second list where the first is empty
+    list = list2;
+    cnt = *count2;
+  }
   const int tid = threadIdx.x;
   const T s = static_cast<T>(hdr[H_SCALE]);
   constexpr int64_t kQB = static_cast<int64_t>(kWG) * Q;
@@ -585,6 +591,54 @@ __global__ __launch_bounds__(kWG) void k_fwd_fixmerge(const int* __restrict__ li
   }
 }
 
+// Bounding box, largest |value| and header in one workgroup, for n <= kSmallBoxMax.
+template <typename T, int DIM, int L>
+__global__ __launch_bounds__(kSmallBox) void k_bbox_small(DevPts data, int64_t n, double p, int f32s, int rel,
+                                                          double* __restrict__ hdr) {
+  constexpr int NV = 2 * DIM + 1;  // minima (negated), maxima, largest |value|: all by max
+  __shared__ T red[kSmallBox / 64][NV];
+  T v[NV];
+#pragma unroll
+  for (int d = 0; d < 2 * DIM; ++d) v[d] = -infT<T>();
+  v[2 * DIM] = T(0);
+  constexpr int kPer = static_cast<int>(kSmallBoxMax / kSmallBox);
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    const int64_t j = static_cast<int64_t>(u) * kSmallBox + threadIdx.x;
+    if (j < n) {
+      T c[3] = {T(0), T(0), T(0)}, z;
+      Loader<T, DIM, L>::data(data, j, c, z);
+#pragma unroll
+      for (int d = 0; d < DIM; ++d) {
+        v[d] = maxT(v[d], -c[d]);
+        v[DIM + d] = maxT(v[DIM + d], c[d]);
+      }
+      v[2 * DIM] = maxT(v[2 * DIM], z < T(0) ? -z : z);
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < NV; ++k)
+#pragma unroll
+    for (int x = 1; x < 64; x <<= 1) v[k] = maxT(v[k], __shfl_xor(v[k], x));
+  const int wave = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 0)
+#pragma unroll
+    for (int k = 0; k < NV; ++k) red[wave][k] = v[k];
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < kSmallBox / 64; ++w)
+#pragma unroll
+      for (int k = 0; k < NV; ++k) v[k] = maxT(v[k], red[w][k]);
+    double mn[3] = {0.0, 0.0, 0.0}, mx[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int d = 0; d < DIM; ++d) {
+      mn[d] = -static_cast<double>(v[d]);
+      mx[d] = static_cast<double>(v[DIM + d]);
+    }
+    finish_header(hdr, mn, mx, DIM, static_cast<double>(v[2 * DIM]), p, f32s != 0, rel != 0);
+  }
+}
+
 // Per-workgroup bounding box of the data coordinates and largest |value|, in the
 // kBboxStride-double record of each workgroup.
 template <typename T, int DIM, int L>
@@ -738,15 +792,14 @@ hipError_t launch_near_check_t(const NearArgs& a, hipStream_t st) {
   const unsigned gl = static_cast<unsigned>(a.m < 64 * kWG ? (a.m + kWG - 1) / kWG + 1 : 64);
   const int* list = a.all ? nullptr : a.list;
   if (!a.all && !a.list) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((k_near_init<T>), dim3(gl), dim3(kWG), 0, st, list, a.count, a.m, a.minb);
+  if (a.init)
+    hipLaunchKernelGGL((k_near_init<T>), dim3(gl), dim3(kWG), 0, st, list, a.count, a.m, a.minb);
   if (a.excl)
     hipLaunchKernelGGL((k_near_check<T, DIM, L, Q, true>), dim3(kNearGrid), dim3(kWG), 0, st, a.data, a.n,
-                       a.query, list, a.count, a.m, a.hdr, a.minb);
+                       a.query, list, a.count, a.list2, a.count2, a.m, a.hdr, a.minb);
   else
     hipLaunchKernelGGL((k_near_check<T, DIM, L, Q, false>), dim3(kNearGrid), dim3(kWG), 0, st, a.data, a.n,
-                       a.query, list, a.count, a.m, a.hdr, a.minb);
-  if (!a.all)
-    hipLaunchKernelGGL((k_near_finish<T>), dim3(gl), dim3(kWG), 0, st, a.list, a.count, a.minb, a.hdr, a.route);
+                       a.query, list, a.count, a.list2, a.count2, a.m, a.hdr, a.minb);
   return hipGetLastError();
 }
 
@@ -756,21 +809,23 @@ hipError_t launch_near_check(const NearArgs& a, hipStream_t st) {
   return a.dim == 3 ? launch_near_check_t<float, 3, L>(a, st) : launch_near_check_t<float, 2, L>(a, st);
 }
 
-template <int L>
-hipError_t launch_bbox(const DevPts& d, int64_t n, int dim, bool f64, double* part, int nb,
-                       hipStream_t st) {
-  if (f64) {
-    if (dim == 3)
-      hipLaunchKernelGGL((k_bbox<double, 3, L>), dim3(nb), dim3(kWG), 0, st, d, n, part);
-    else
-      hipLaunchKernelGGL((k_bbox<double, 2, L>), dim3(nb), dim3(kWG), 0, st, d, n, part);
-  } else {
-    if (dim == 3)
-      hipLaunchKernelGGL((k_bbox<float, 3, L>), dim3(nb), dim3(kWG), 0, st, d, n, part);
-    else
-      hipLaunchKernelGGL((k_bbox<float, 2, L>), dim3(nb), dim3(kWG), 0, st, d, n, part);
+// The header of a call: one kernel for few data points, else per-workgroup boxes and their
+// reduction (idw_common.hip).
+template <typename T, int DIM, int L>
+hipError_t launch_header_t(const HeaderArgs& a, hipStream_t st) {
+  if (a.n <= kSmallBoxMax) {
+    hipLaunchKernelGGL((k_bbox_small<T, DIM, L>), dim3(1), dim3(kSmallBox), 0, st, a.data, a.n, a.p,
+                       sizeof(T) == 4 ? 1 : 0, a.rel ? 1 : 0, a.hdr);
+    return hipGetLastError();
   }
-  return hipGetLastError();
+  hipLaunchKernelGGL((k_bbox<T, DIM, L>), dim3(a.nblocks), dim3(kWG), 0, st, a.data, a.n, a.part);
+  return bbox_final(a.part, a.nblocks, DIM, a.p, sizeof(T) == 4, a.rel, a.hdr, st);
+}
+
+template <int L>
+hipError_t launch_header(const HeaderArgs& a, int dim, bool f64, hipStream_t st) {
+  if (f64) return dim == 3 ? launch_header_t<double, 3, L>(a, st) : launch_header_t<double, 2, L>(a, st);
+  return dim == 3 ? launch_header_t<float, 3, L>(a, st) : launch_header_t<float, 2, L>(a, st);
 }
 
 }  // namespace idw

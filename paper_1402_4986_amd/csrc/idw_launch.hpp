@@ -87,12 +87,36 @@ struct NearArgs {
   int dim = 2;
   bool f64 = false;
   bool excl = false;
-  const int* list = nullptr;   // candidate query indices
-  const int* count = nullptr;  // number of candidates (device)
+  const int* list = nullptr;   // query indices
+  const int* count = nullptr;  // number of them (device)
+  const int* list2 = nullptr;  // taken instead where the first count is 0 (nullable)
+  const int* count2 = nullptr;
   const double* hdr = nullptr;
-  uint8_t* route = nullptr;    // [m] QueryRoute, settled for the candidates
-  unsigned long long* minb = nullptr;  // [m] per-candidate minimum (bits), scratch
-  bool all = false;  // every query 0..m-1 (list and count unused); no route is written
+  unsigned long long* minb = nullptr;  // [m] per-query minimum (bits)
+  bool all = false;   // every query 0..m-1 (the lists and counts unused)
+  bool init = false;  // set the minima to +inf first
+};
+
+// The header kernels (bounding box, thresholds, cleared counts).
+struct HeaderArgs {
+  DevPts data;
+  int64_t n = 0;
+  double p = 2.0;
+  bool rel = false;
+  double* part = nullptr;  // [nblocks] partial boxes
+  int nblocks = 1;
+  double* hdr = nullptr;
+};
+
+// Per-query routes and lists.
+struct RouteArgs {
+  int64_t m = 0;
+  const double* hdr = nullptr;
+  int* hint = nullptr;      // header int slots
+  uint8_t* route = nullptr; // [m]
+  int* list = nullptr;      // [m] candidates, then the F_FP64 queries
+  int* bcnt = nullptr;      // [m / kCountBlock + 1] scratch
+  unsigned long long* minb = nullptr;  // [m]
 };
 
 // The grid of the nearest-distance searches (idw_grid.hpp).
@@ -126,8 +150,7 @@ constexpr int kCountBlock = 4096; // flags per compaction block (16 per thread)
 #define IDW_DECLARE_LAYOUT(NAME)                                                 \
   hipError_t fwd_sweep_##NAME(const FwdArgs& a, bool f64, hipStream_t st);       \
   hipError_t fwd_fixup_##NAME(const FwdArgs& a, bool f64, hipStream_t st);       \
-  hipError_t bbox_##NAME(const DevPts& d, int64_t n, int dim, bool f64, double* part, \
-                         int nblocks, hipStream_t st);                           \
+  hipError_t header_##NAME(const HeaderArgs& a, int dim, bool f64, hipStream_t st); \
   hipError_t bwd_query_##NAME(const BwdArgs& a, bool f64, hipStream_t st);       \
   hipError_t bwd_data_##NAME(const BwdArgs& a, bool f64, hipStream_t st);        \
   hipError_t bwd_datax_##NAME(const BwdArgs& a, bool f64, hipStream_t st);       \
@@ -145,20 +168,22 @@ IDW_DECLARE_LAYOUT(soaos)
 // Layout-independent kernels (idw_common.hip).
 hipError_t bbox_final(const double* part, int nblocks, int dim, double p, bool f32_scaling,
                       bool rel, double* hdr, hipStream_t st);
-hipError_t merge_split(const double2* part, int64_t m, int split, const double* hdr,
-                       void* out_z, bool f64, double* out_den, uint8_t* flag, hipStream_t st);
+// The split partials' merge, or (split 1) the sweep's own routes: collects the candidates too.
+hipError_t merge_split(const FwdArgs& a, const RouteArgs& r, bool f64, hipStream_t st);
+// Routes from the saved denominators, candidates collected.
+hipError_t flags_from_den(const double* den, const RouteArgs& r, bool f64, hipStream_t st);
+// Settles the candidates by their minima and lists the F_FP64 queries in ascending order.
+hipError_t settle(const RouteArgs& r, bool f64, hipStream_t st);
 hipError_t compact_flags(const uint8_t* flag, int64_t m, int* bcnt, int* list, int* count,
                          uint8_t want, hipStream_t st);
-hipError_t flags_from_den(const double* den, int64_t m, const double* hdr, uint8_t* flag,
-                          hipStream_t st);
-hipError_t bwd_qmerge(const BwdArgs& a, bool f64, hipStream_t st);
-hipError_t bwd_zmerge(const BwdArgs& a, bool f64, hipStream_t st);
-hipError_t bwd_xmerge(const BwdArgs& a, int split, bool f64, hipStream_t st);
+// The merges of the adjoint's partials that were requested, in one launch: grad_q and the dp
+// partials (query), grad_z (data), grad_x (its partials are a.split_z rows).
+hipError_t bwd_merge(const BwdArgs& a, bool query, bool data, bool x, bool f64, hipStream_t st);
 hipError_t dp_final(const double* wg_dp, int nwg, const double* slot_dp, const int* count,
                     double* grad_p, hipStream_t st);
-// Grid geometry and the per-call gates (mode 0: candidate check of hint[0] candidates; mode
-// 1: ring search of all m queries), then the exclusive scan of the cell counts.
-hipError_t grid_setup(const GridArgs& a, int mode, bool grid_on, hipStream_t st);
+// Grid geometry, the per-call gates (mode 0: candidate check; mode 1: ring search of all m
+// queries) and cleared counts; then the exclusive scan of the cell counts.
+hipError_t grid_setup(const GridArgs& a, int mode, const int* ncand, hipStream_t st);
 hipError_t grid_scan(const GridArgs& a, hipStream_t st);
 
 }  // namespace idw

@@ -24,9 +24,8 @@ hipError_t IDW_CAT(fwd_fixup_, IDW_LAYOUT_NAME)(const FwdArgs& a, bool f64, hipS
   return launch_fwd_fixup<IDW_LAYOUT>(a, f64, st);
 }
 
-hipError_t IDW_CAT(bbox_, IDW_LAYOUT_NAME)(const DevPts& d, int64_t n, int dim, bool f64,
-                                           double* part, int nblocks, hipStream_t st) {
-  return launch_bbox<IDW_LAYOUT>(d, n, dim, f64, part, nblocks, st);
+hipError_t IDW_CAT(header_, IDW_LAYOUT_NAME)(const HeaderArgs& a, int dim, bool f64, hipStream_t st) {
+  return launch_header<IDW_LAYOUT>(a, dim, f64, st);
 }
 
 hipError_t IDW_CAT(bwd_query_, IDW_LAYOUT_NAME)(const BwdArgs& a, bool f64, hipStream_t st) {
