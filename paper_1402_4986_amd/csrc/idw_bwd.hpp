@@ -125,20 +125,136 @@ __device__ __forceinline__ T wr_times(T t, T c, T f) {
     return t * f;
 }
 
-// One LDS tile of the query sweep.  `cnt` records are valid (all of them unless TAIL).
+// w, f and log2(r2) of N pairs (wterms), their transcendentals in one run.
+template <int PM, bool NDQ, bool NDP, int N>
+__device__ __forceinline__ void wterms_run(const float (&r2)[N], float nhp, float (&w)[N], float (&f)[N],
+                                           float (&lg)[N]) {
+  run_begin();
+  if constexpr (PM == PM_GEN) {
+    const float e = NDQ ? nhp - 1.0f : nhp;
+#pragma unroll
+    for (int i = 0; i < N; ++i) lg[i] = __builtin_amdgcn_logf(r2[i]);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < N; ++i) f[i] = e * lg[i];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < N; ++i) f[i] = __builtin_amdgcn_exp2f(f[i]);
+  } else {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      if constexpr (PM == PM_2 || PM == PM_4)
+        w[i] = __builtin_amdgcn_rcpf(r2[i]);
+      else
+        w[i] = __builtin_amdgcn_rsqf(r2[i]);
+    }
+    if constexpr (NDP) {
+#pragma unroll
+      for (int i = 0; i < N; ++i) lg[i] = __builtin_amdgcn_logf(r2[i]);
+    }
+    if constexpr (PM == PM_25) {
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < N; ++i) f[i] = __builtin_amdgcn_sqrtf(w[i]);
+    }
+  }
+  run_end();
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    if constexpr (PM == PM_GEN) {
+      w[i] = NDQ ? f[i] * r2[i] : f[i];
+    } else if constexpr (PM == PM_2) {
+      f[i] = w[i];
+    } else if constexpr (PM == PM_1) {
+      f[i] = w[i] * w[i];
+    } else if constexpr (PM == PM_3) {
+      f[i] = w[i] * w[i];
+      w[i] = f[i] * w[i];
+    } else if constexpr (PM == PM_4) {
+      f[i] = w[i];
+      w[i] = w[i] * w[i];
+    } else {  // PM_25
+      const float s2 = w[i] * w[i];
+      w[i] = s2 * f[i];
+      f[i] = s2;
+    }
+  }
+}
+
+// Whole 64-record blocks [0, end) of the query sweep in FP32 without a self pair: groups of 4
+// records whose transcendentals form one run (idw_phase.hpp); the operations of bwdq_tile.
+// 131,072 x 131,072 at p = 1.5, dp alone (a leave-one-out fit): 4.79 -> 3.68 ms, 33.7 cycles a
+// pair and wave of the 33 that 8 plain instructions and two transcendentals take.
+template <int DIM, int PM, int Q, bool NDP, bool NDQ>
+__device__ __forceinline__ void bwdq_tile_run(const RecTile<float, DIM, kTile>& tl, int end, const float (&qc)[Q][3],
+                                              const float (&zq)[Q], float nhp, BlockSum<float> (&P)[Q],
+                                              BlockSum<float> (&G)[Q][3]) {
+  constexpr int CH = 64, GR = 4, N = GR * Q;
+#pragma unroll 1
+  for (int c0 = 0; c0 < end; c0 += CH) {
+    float ap[Q], ag[Q][3];
+#pragma unroll
+    for (int k = 0; k < Q; ++k) ap[k] = ag[k][0] = ag[k][1] = ag[k][2] = 0.f;
+#pragma unroll 4
+    for (int j = 0; j < CH; j += GR) {
+      RecGroup<DIM, GR> d;
+      d.load(tl, c0 + j);
+      float e[3][N], r2[N], w[N], f[N], lg[N];
+#pragma unroll
+      for (int g = 0; g < GR; ++g)
+#pragma unroll
+        for (int k = 0; k < Q; ++k) {
+          const int i = g * Q + k;
+          e[0][i] = qc[k][0] - d.x[g];
+          e[1][i] = qc[k][1] - d.y[g];
+          r2[i] = e[0][i] * e[0][i];
+          r2[i] = fmaf(e[1][i], e[1][i], r2[i]);
+          if constexpr (DIM == 3) {
+            e[2][i] = qc[k][2] - d.z[g];
+            r2[i] = fmaf(e[2][i], e[2][i], r2[i]);
+          }
+        }
+      wterms_run<PM, NDQ, NDP, N>(r2, nhp, w, f, lg);
+#pragma unroll
+      for (int g = 0; g < GR; ++g)
+#pragma unroll
+        for (int k = 0; k < Q; ++k) {
+          const int i = g * Q + k;
+          const float c = d.v[g] - zq[k];
+          const float t = w[i] * c;
+          if constexpr (NDP) ap[k] = fmaf(t, lg[i], ap[k]);
+          if constexpr (NDQ) {
+            const float u = wr_times<PM>(t, c, f[i]);
+#pragma unroll
+            for (int x = 0; x < DIM; ++x) ag[k][x] = fmaf(u, e[x][i], ag[k][x]);
+          }
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < Q; ++k) {
+      if constexpr (NDP) P[k].add(ap[k]);
+      if constexpr (NDQ) {
+#pragma unroll
+        for (int x = 0; x < DIM; ++x) G[k][x].add(ag[k][x]);
+      }
+    }
+  }
+}
+
+// One LDS tile of the query sweep, its records [begin, cnt) with begin a multiple of 64 (whole
+// blocks unless TAIL).
 template <typename T, int DIM, int PM, int Q, bool DIAG, bool TAIL, bool NDP, bool NDQ, int UNR>
-__device__ __forceinline__ void bwdq_tile(const P4<T>* __restrict__ tl, int cnt, int64_t jt,
+__device__ __forceinline__ void bwdq_tile(const RecTile<T, DIM, kTile>& tl, int begin, int cnt, int64_t jt,
                                           const T (&qc)[Q][3], const T (&zq)[Q],
                                           const int64_t (&qi)[Q], T nhp, BlockSum<T> (&P)[Q],
                                           BlockSum<T> (&G)[Q][3]) {
   constexpr int CH = 64;
   const int lim = TAIL ? cnt : kTile;
   // One 64-record block at a time, merged before the next: unrolled over the tile, the
-  // compiler keeps every block's sums live to the tile's end (FP32 p = 2 with dp and dq:
-  // 127 VGPRs against 78; FP64: 249 against 148).  Measured at 1M x 1M, block by block is
-  // 2% faster for dq alone in FP32 and 3% for the FP64 query + data sweeps.
+  // compiler keeps every block's sums live to the tile's end (FP64: 249 VGPRs against 148;
+  // block by block is 3% faster for the query + data sweeps at 1M x 1M).
 #pragma unroll 1
-  for (int c0 = 0; c0 < lim; c0 += CH) {
+  for (int c0 = begin; c0 < lim; c0 += CH) {
     T ap[Q], ag[Q][3];
 #pragma unroll
     for (int k = 0; k < Q; ++k) {
@@ -148,7 +264,7 @@ __device__ __forceinline__ void bwdq_tile(const P4<T>* __restrict__ tl, int cnt,
     const int ce = TAIL ? ((lim - c0) < CH ? (lim - c0) : CH) : CH;
 #pragma unroll UNR
     for (int jj = 0; jj < ce; ++jj) {
-      const P4<T> d = tl[c0 + jj];
+      const P4<T> d = tl.get(c0 + jj);
       const T dv = (DIM == 3) ? d.w : d.z;
 #pragma unroll
       for (int k = 0; k < Q; ++k) {
@@ -191,23 +307,22 @@ __device__ __forceinline__ void bwdq_tile(const P4<T>* __restrict__ tl, int cnt,
   }
 }
 
-// Query sweep: writes part[c * m + i] = (P, Gx, Gy, Gz) in scaled units (double).
-// Measured on MI355X: FP32 Q = 2, unroll 4, >= 2 waves per SIMD (13.8 lane-slots per pair
-// for 2-D p = 2 with dp and dq, against 14.6 for Q = 4).
+// Query sweep: writes part[c * m + i] = (P, Gx, Gy, Gz) in scaled units (double).  Q = 2; FP32
+// at 4 waves per SIMD (idw_phase.hpp), FP64 unrolled 4 deep at 2 or more.
 template <typename T, int Q>
 struct QueryTune {
   static constexpr int UNR = 4;
-  static constexpr int WPE = (Q <= 2) ? 2 : 1;
+  static constexpr int WMIN = sizeof(T) == 4 ? 4 : 2;
+  static constexpr int WMAX = sizeof(T) == 4 ? 4 : 8;
 };
 
-template <typename T, int DIM, int L, int PM, int Q, bool NDP, bool NDQ,
-          int UNR = QueryTune<T, Q>::UNR, int WPE = QueryTune<T, Q>::WPE>
-__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(WPE, 8))) void k_bwd_query(DevPts data, int64_t n, DevPts query, int64_t m,
+template <typename T, int DIM, int L, int PM, int Q, bool NDP, bool NDQ, typename Tune = QueryTune<T, Q>>
+__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(Tune::WMIN, Tune::WMAX))) void k_bwd_query(DevPts data, int64_t n, DevPts query, int64_t m,
                                                    int64_t chunk, T nhp, unsigned flags,
                                                    const double* __restrict__ hdr,
                                                    const T* __restrict__ saved_z,
                                                    double4* __restrict__ part) {
-  __shared__ P4<T> tile[2][kTile];
+  __shared__ RecTile<T, DIM, kTile> tile[2];
   const int tid = threadIdx.x;
   const int64_t q0 = static_cast<int64_t>(blockIdx.x) * (kWG * Q);
   const int64_t jb = static_cast<int64_t>(blockIdx.y) * chunk;
@@ -248,7 +363,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(WPE, 8))) v
   };
   auto put = [&](int b) {
 #pragma unroll
-    for (int u = 0; u < 2; ++u) tile[b][u * kWG + tid] = stage<T, DIM>(rc[u], rv[u], s);
+    for (int u = 0; u < 2; ++u) tile[b].put(u * kWG + tid, stage<T, DIM>(rc[u], rv[u], s));
   };
 
   const int ntiles = static_cast<int>((je - jb + kTile - 1) / kTile);
@@ -265,16 +380,17 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(WPE, 8))) v
     const int64_t jt = jb + static_cast<int64_t>(t) * kTile;
     const int cnt = static_cast<int>((je - jt) < kTile ? (je - jt) : kTile);
     const bool diag = excl && jt < q0 + kWG * Q && q0 < jt + kTile;
-    if (cnt < kTile) {
-      if (diag)
-        bwdq_tile<T, DIM, PM, Q, true, true, NDP, NDQ, 1>(tile[t & 1], cnt, jt, qc, zq, qi, nhp, P, G);
-      else
-        bwdq_tile<T, DIM, PM, Q, false, true, NDP, NDQ, 1>(tile[t & 1], cnt, jt, qc, zq, qi, nhp, P, G);
+    const auto& tl = tile[t & 1];
+    if (diag) {
+      bwdq_tile<T, DIM, PM, Q, true, true, NDP, NDQ, 1>(tl, 0, cnt, jt, qc, zq, qi, nhp, P, G);
     } else {
-      if (diag)
-        bwdq_tile<T, DIM, PM, Q, true, false, NDP, NDQ, 1>(tile[t & 1], cnt, jt, qc, zq, qi, nhp, P, G);
-      else
-        bwdq_tile<T, DIM, PM, Q, false, false, NDP, NDQ, UNR>(tile[t & 1], cnt, jt, qc, zq, qi, nhp, P, G);
+      const int whole = cnt & ~63;
+      if constexpr (sizeof(T) == 4)
+        bwdq_tile_run<DIM, PM, Q, NDP, NDQ>(tl, whole, qc, zq, nhp, P, G);
+      else if (whole == kTile)
+        bwdq_tile<T, DIM, PM, Q, false, false, NDP, NDQ, Tune::UNR>(tl, 0, kTile, jt, qc, zq, qi, nhp, P, G);
+      const int done = sizeof(T) == 4 || whole == kTile ? whole : 0;
+      if (done < cnt) bwdq_tile<T, DIM, PM, Q, false, true, NDP, NDQ, 1>(tl, done, cnt, jt, qc, zq, qi, nhp, P, G);
     }
     if (t + 1 < ntiles) put((t + 1) & 1);
     __syncthreads();
@@ -339,9 +455,39 @@ __device__ __forceinline__ void bwd_qmerge_block(int64_t block, const double4* _
   if (threadIdx.x == 0) wg_dp[block] = tot;
 }
 
+// The whole tile of the data sweep in FP32 without a self pair, in runs (idw_phase.hpp).
+template <int DIM, int PM, int Q>
+__device__ __forceinline__ void bwdd_tile_run(const RecTile<float, DIM, kTile>& tl, const float (&xc)[Q][3], float nhp,
+                                              BlockSum<float> (&Zs)[Q]) {
+  constexpr int CH = 64, GR = 4;
+#pragma unroll 1
+  for (int c0 = 0; c0 < kTile; c0 += CH) {
+    float az[Q];
+#pragma unroll
+    for (int k = 0; k < Q; ++k) az[k] = 0.f;
+#pragma unroll 4
+    for (int j = 0; j < CH; j += GR) {
+      RecGroup<DIM, GR> d;
+      d.load(tl, c0 + j);
+      float w[GR * Q];
+#pragma unroll
+      for (int g = 0; g < GR; ++g)
+#pragma unroll
+        for (int k = 0; k < Q; ++k) w[g * Q + k] = d.r2(xc[k], g);
+      weight_run<PM>(w, nhp);
+#pragma unroll
+      for (int g = 0; g < GR; ++g)
+#pragma unroll
+        for (int k = 0; k < Q; ++k) az[k] = fmaf(d.v[g], w[g * Q + k], az[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < Q; ++k) Zs[k].add(az[k]);
+  }
+}
+
 // One LDS tile of the data sweep: for the lane's Q data points, accumulate a_i * w_ij.
 template <typename T, int DIM, int PM, int Q, bool DIAG, int UNR>
-__device__ __forceinline__ void bwdd_tile(const P4<T>* __restrict__ tl, int64_t it,
+__device__ __forceinline__ void bwdd_tile(const RecTile<T, DIM, kTile>& tl, int64_t it,
                                           const T (&xc)[Q][3], const int64_t (&xj)[Q], T nhp,
                                           BlockSum<T> (&Zs)[Q]) {
   constexpr int CH = 64;
@@ -351,7 +497,7 @@ __device__ __forceinline__ void bwdd_tile(const P4<T>* __restrict__ tl, int64_t 
     for (int k = 0; k < Q; ++k) az[k] = T(0);
 #pragma unroll UNR
     for (int ii = 0; ii < CH; ++ii) {
-      const P4<T> d = tl[c0 + ii];
+      const P4<T> d = tl.get(c0 + ii);
       const T a = (DIM == 3) ? d.w : d.z;
 #pragma unroll
       for (int k = 0; k < Q; ++k) {
@@ -368,24 +514,24 @@ __device__ __forceinline__ void bwdd_tile(const P4<T>* __restrict__ tl, int64_t 
   }
 }
 
-// Data sweep: part[c * n + j] = sum over query chunk c of a_i w_ij (double).
-// Measured on MI355X: FP32 Q = 4, unroll 4, >= 2 waves per SIMD (6.8 lane-slots per pair).
+// Data sweep: part[c * n + j] = sum over query chunk c of a_i w_ij (double).  FP32 Q = 4 at 4
+// waves per SIMD (idw_phase.hpp), FP64 Q = 2, unrolled 4 deep at 2 or more.
 template <typename T, int Q>
 struct DataTune {
   static constexpr int UNR = 4;
-  static constexpr int WPE = 2;
+  static constexpr int WMIN = sizeof(T) == 4 ? 4 : 2;
+  static constexpr int WMAX = sizeof(T) == 4 ? 4 : 8;
 };
 
-template <typename T, int DIM, int L, int PM, int Q, int UNR = DataTune<T, Q>::UNR,
-          int WPE = DataTune<T, Q>::WPE>
-__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(WPE, 8))) void k_bwd_data(DevPts data, int64_t n, DevPts query, int64_t m,
+template <typename T, int DIM, int L, int PM, int Q, typename Tune = DataTune<T, Q>>
+__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(Tune::WMIN, Tune::WMAX))) void k_bwd_data(DevPts data, int64_t n, DevPts query, int64_t m,
                                                   int64_t chunk, T nhp, unsigned flags,
                                                   const double* __restrict__ hdr,
                                                   const T* __restrict__ grad_out,
                                                   const double* __restrict__ saved_den,
                                                   double* __restrict__ part,
                                                   const uint8_t* __restrict__ route) {
-  __shared__ P4<T> tile[2][kTile];
+  __shared__ RecTile<T, DIM, kTile> tile[2];
   const int tid = threadIdx.x;
   const int64_t x0 = static_cast<int64_t>(blockIdx.x) * (kWG * Q);
   const int64_t ib = static_cast<int64_t>(blockIdx.y) * chunk;
@@ -429,7 +575,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(WPE, 8))) v
   };
   auto put = [&](int b) {
 #pragma unroll
-    for (int u = 0; u < 2; ++u) tile[b][u * kWG + tid] = stage<T, DIM>(rc[u], ra[u], s);
+    for (int u = 0; u < 2; ++u) tile[b].put(u * kWG + tid, stage<T, DIM>(rc[u], ra[u], s));
   };
 
   const int ntiles = static_cast<int>((ie - ib + kTile - 1) / kTile);
@@ -444,8 +590,10 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(WPE, 8))) v
     const bool diag = excl && it < x0 + kWG * Q && x0 < it + kTile;
     if (diag)
       bwdd_tile<T, DIM, PM, Q, true, 1>(tile[t & 1], it, xc, xj, nhp, Zs);
+    else if constexpr (sizeof(T) == 4)
+      bwdd_tile_run<DIM, PM, Q>(tile[t & 1], xc, nhp, Zs);
     else
-      bwdd_tile<T, DIM, PM, Q, false, UNR>(tile[t & 1], it, xc, xj, nhp, Zs);
+      bwdd_tile<T, DIM, PM, Q, false, Tune::UNR>(tile[t & 1], it, xc, xj, nhp, Zs);
     if (t + 1 < ntiles) put((t + 1) & 1);
     __syncthreads();
   }
@@ -923,38 +1071,21 @@ template <typename T, int DIM, int L, int PM>
 hipError_t launch_bwd_query_t(const BwdArgs& a, int split, int64_t chunk, double4* part,
                               hipStream_t st) {
   const bool ndp = (a.flags & 0x4u) != 0, ndq = (a.flags & 0x8u) != 0;
-  const int Q = a.q_per_lane;
+  constexpr int Q = 2;
+  if (a.q_per_lane != Q) return hipErrorInvalidValue;
   const int64_t qpb = static_cast<int64_t>(kWG) * Q;
   dim3 grid(static_cast<unsigned>((a.m + qpb - 1) / qpb), static_cast<unsigned>(split));
   const T nhp = static_cast<T>(-0.5 * a.p);
   const T* sz = static_cast<const T*>(a.saved_z);
-#define IDW_BQ(QQ, DP, DQ)                                                                  \
-  hipLaunchKernelGGL((k_bwd_query<T, DIM, L, PM, QQ, DP, DQ>), grid, dim3(kWG), 0, st,      \
-                     a.data, a.n, a.query, a.m, chunk, nhp, a.flags, a.hdr, sz, part)
-#define IDW_BQ_Q(QQ)                  \
-  case QQ:                            \
-    if (ndp && ndq)                   \
-      IDW_BQ(QQ, true, true);         \
-    else if (ndp)                     \
-      IDW_BQ(QQ, true, false);        \
-    else                              \
-      IDW_BQ(QQ, false, true);        \
-    break;
-  if constexpr (sizeof(T) == 4) {
-    switch (Q) {
-      IDW_BQ_Q(2)
-      IDW_BQ_Q(4)
-      default:
-        return hipErrorInvalidValue;
-    }
-  } else {
-    switch (Q) {
-      IDW_BQ_Q(2)
-      default:
-        return hipErrorInvalidValue;
-    }
-  }
-#undef IDW_BQ_Q
+#define IDW_BQ(DP, DQ)                                                                            \
+  hipLaunchKernelGGL((k_bwd_query<T, DIM, L, PM, Q, DP, DQ>), grid, dim3(kWG), 0, st, a.data, a.n, \
+                     a.query, a.m, chunk, nhp, a.flags, a.hdr, sz, part)
+  if (ndp && ndq)
+    IDW_BQ(true, true);
+  else if (ndp)
+    IDW_BQ(true, false);
+  else
+    IDW_BQ(false, true);
 #undef IDW_BQ
   return hipGetLastError();
 }
@@ -962,31 +1093,14 @@ hipError_t launch_bwd_query_t(const BwdArgs& a, int split, int64_t chunk, double
 template <typename T, int DIM, int L, int PM>
 hipError_t launch_bwd_data_t(const BwdArgs& a, int split, int64_t chunk, double* part,
                              hipStream_t st) {
-  const int Q = a.q_per_lane;
+  constexpr int Q = sizeof(T) == 4 ? 4 : 2;
+  if (a.q_per_lane != Q) return hipErrorInvalidValue;
   const int64_t xpb = static_cast<int64_t>(kWG) * Q;
   dim3 grid(static_cast<unsigned>((a.n + xpb - 1) / xpb), static_cast<unsigned>(split));
   const T nhp = static_cast<T>(-0.5 * a.p);
   const T* go = static_cast<const T*>(a.grad_out);
-#define IDW_BD_Q(QQ)                                                                        \
-  case QQ:                                                                                  \
-    hipLaunchKernelGGL((k_bwd_data<T, DIM, L, PM, QQ>), grid, dim3(kWG), 0, st, a.data,     \
-                       a.n, a.query, a.m, chunk, nhp, a.flags, a.hdr, go, a.saved_den, part, a.route); \
-    break;
-  if constexpr (sizeof(T) == 4) {
-    switch (Q) {
-      IDW_BD_Q(4)
-      IDW_BD_Q(8)
-      default:
-        return hipErrorInvalidValue;
-    }
-  } else {
-    switch (Q) {
-      IDW_BD_Q(2)
-      default:
-        return hipErrorInvalidValue;
-    }
-  }
-#undef IDW_BD_Q
+  hipLaunchKernelGGL((k_bwd_data<T, DIM, L, PM, Q>), grid, dim3(kWG), 0, st, a.data, a.n, a.query, a.m, chunk, nhp,
+                     a.flags, a.hdr, go, a.saved_den, part, a.route);
   return hipGetLastError();
 }
 

@@ -309,62 +309,6 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE, 8))) vo
 // dx 462 -> 391, p = 1.5 404 -> 335, p = 8 (relative weights) 458 -> 402.
 // ---------------------------------------------------------------------------------------
 
-// w, f and log2(r2) of N pairs (wterms), their transcendentals in one run.
-template <int PM, bool NDQ, bool NDP, int N>
-__device__ __forceinline__ void wterms_run(const float (&r2)[N], float nhp, float (&w)[N], float (&f)[N],
-                                           float (&lg)[N]) {
-  run_begin();
-  if constexpr (PM == PM_GEN) {
-    const float e = NDQ ? nhp - 1.0f : nhp;
-#pragma unroll
-    for (int i = 0; i < N; ++i) lg[i] = __builtin_amdgcn_logf(r2[i]);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int i = 0; i < N; ++i) f[i] = e * lg[i];
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int i = 0; i < N; ++i) f[i] = __builtin_amdgcn_exp2f(f[i]);
-  } else {
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-      if constexpr (PM == PM_2 || PM == PM_4)
-        w[i] = __builtin_amdgcn_rcpf(r2[i]);
-      else
-        w[i] = __builtin_amdgcn_rsqf(r2[i]);
-    }
-    if constexpr (NDP) {
-#pragma unroll
-      for (int i = 0; i < N; ++i) lg[i] = __builtin_amdgcn_logf(r2[i]);
-    }
-    if constexpr (PM == PM_25) {
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int i = 0; i < N; ++i) f[i] = __builtin_amdgcn_sqrtf(w[i]);
-    }
-  }
-  run_end();
-#pragma unroll
-  for (int i = 0; i < N; ++i) {
-    if constexpr (PM == PM_GEN) {
-      w[i] = NDQ ? f[i] * r2[i] : f[i];
-    } else if constexpr (PM == PM_2) {
-      f[i] = w[i];
-    } else if constexpr (PM == PM_1) {
-      f[i] = w[i] * w[i];
-    } else if constexpr (PM == PM_3) {
-      f[i] = w[i] * w[i];
-      w[i] = f[i] * w[i];
-    } else if constexpr (PM == PM_4) {
-      f[i] = w[i];
-      w[i] = w[i] * w[i];
-    } else {  // PM_25
-      const float s2 = w[i] * w[i];
-      w[i] = s2 * f[i];
-      f[i] = s2;
-    }
-  }
-}
-
 // Queries per wave: as many as the registers of 4 waves per SIMD hold.  16 in 2-D (48 sums) and
 // in 3-D (64 sums; 131,072 x 1M points, p = 2: 47.0 ms against 49.0 with 8); 8 where the scales
 // of the relative weights or the 3-D X sums would make 16 spill.
