@@ -203,6 +203,22 @@ __device__ __forceinline__ double rsq64_w(double a) {
   return fma(0.5 * y, fma(-t, y, 1.0), y);
 }
 
+// The reciprocals of four FP64 values from one: 1/(abcd) by rcp64_w, then 9 multiplies instead
+// of three more estimates and Newton steps, 64.7 issue cycles for the four against 100.4 (an
+// estimate takes 16.3, every other FP64 instruction 4.4).  The weights' error stays that of the
+// one Newton step (rcp64_w); the products add about 1e-16.  A zero or non-finite value, or a
+// product outside the FP64 range, makes all four NaN, infinite or zero-times-infinite: the four
+// belong to one query, whose denominator then turns NaN or infinite and which the FP64 fix-up
+// recomputes (an exact hit, a point nearer than 1e-70 of the extent, or a query 1e38 extents
+// away).
+__device__ __forceinline__ void rcp64_w4(double (&a)[4]) {
+  const double p = a[0] * a[1], q = a[2] * a[3];
+  const double y = rcp64_w(p * q);
+  const double yp = y * q, yq = y * p;  // 1/p, 1/q
+  const double r0 = yp * a[1], r1 = yp * a[0], r2 = yq * a[3], r3 = yq * a[2];
+  a[0] = r0, a[1] = r1, a[2] = r2, a[3] = r3;
+}
+
 // log2 and exp2 in the FP64 sweeps (the power gradient's log2 r2 and the general-p weight
 // 2^(-p/2 log2 r2)), from two 256-entry tables in LDS.  Every lane indexes them with its
 // own value; 16-entry tables (conflict-free, but two and four more polynomial terms)
@@ -225,8 +241,9 @@ __device__ __forceinline__ double rsq64_w(double a) {
 //  exp2_t: k = round(256 x), x = k/256 + f with |f| <= 1/512 (exact); 2^x = 2^(k >> 8)
 //    2^((k & 255)/256) 2^f, the table holding 2^(j/256) (rounded) and 2^f its Taylor series
 //    in f ln 2 through the fifth power (truncation below 2^-54); v_ldexp applies 2^(k >> 8),
-//    with the overflow to +inf and the underflow to subnormals and 0.  x = +inf gives +inf
-//    (exact hits), -inf gives 0.
+//    with the overflow to +inf and the underflow to subnormals and 0.  k is read from the low
+//    bits of 256 x + 1.5 2^52 (one fma; |256 x| < 2^25 here, x being an exponent of at most 33
+//    times a log2_t result, which is finite).
 // The tables are static LDS arrays of the kernels that call *_table_init() at their start;
 // those synchronise (after staging their first tile) before the first lookup.
 constexpr int kLogTab = 256;
@@ -273,18 +290,17 @@ __device__ __forceinline__ double log2_t(double a) {
 __device__ __forceinline__ double exp2_t(double x) {
   constexpr double C1 = 0.69314718055994530942;  // ln 2
   constexpr double C2 = C1 * C1 / 2.0, C3 = C2 * C1 / 3.0, C4 = C3 * C1 / 4.0, C5 = C4 * C1 / 5.0;
-  const double xc = fmin(fmax(x, -1100.0), 1100.0);  // NaN -> -1100 (its result is unused)
-  const double kd = rint(xc * kExpTab);
-  const int k = static_cast<int>(kd);
-  const double f = fma(kd, -1.0 / kExpTab, xc);
+  constexpr double kMagic = 0x1.8p52;
+  const double km = fma(x, static_cast<double>(kExpTab), kMagic);
+  const int k = static_cast<int>(static_cast<unsigned int>(__builtin_bit_cast(unsigned long long, km)));
+  const double f = fma(km - kMagic, -1.0 / kExpTab, x);
   double p = C5;
   p = fma(p, f, C4);
   p = fma(p, f, C3);
   p = fma(p, f, C2);
   p = fma(p, f, C1);
   p = fma(p, f, 1.0);
-  const double r = __builtin_amdgcn_ldexp(exp2_table()[k & (kExpTab - 1)] * p, k >> 8);
-  return x == __builtin_huge_val() ? x : r;
+  return __builtin_amdgcn_ldexp(exp2_table()[k & (kExpTab - 1)] * p, k >> 8);
 }
 
 // The general-p weight a^nh (nh = -p/2) in the FP64 sweeps that need no log2 (forward, data
@@ -295,8 +311,10 @@ __device__ __forceinline__ double exp2_t(double x) {
 // 256 entries, library exp2 and pow) and the last as its binomial series through r^10
 // (truncation below 2^-66 for |nh| <= 33).  Against exp2_t(nh log2_t(a)) the FP64 forward's
 // inner loop drops from about 50 to 33 instructions a pair (29 to 19 of them FP64), and the
-// rounding no longer grows with |nh log2 a|.  Zero and subnormal a give +inf (exact or
-// near-coincident hits, settled by the FP64 fix-up).
+// rounding no longer grows with |nh log2 a|.  Zero and subnormal a give +inf (their entry of the
+// first table; exact or near-coincident hits, settled by the FP64 fix-up).  For |nh| <= 3 the
+// series stops at r^6 (kPowLow): the first term left out is below C(9, 7) 2^-63 < 2^-57, under
+// the rounding of the sum.
 constexpr int kPowExp = 2048;
 
 __device__ __forceinline__ double* pow_etable() {
@@ -319,7 +337,9 @@ __device__ __forceinline__ void pow_table_init(double nh) {
     const double e = static_cast<double>(i - 1023);
     const double hi = e * nh;
     const double lo = fma(e, nh, -hi);
-    pow_etable()[i] = i < kPowExp - 1 ? exp2(hi) * fma(lo, 0.69314718055994530942, 1.0) : 0.0;
+    pow_etable()[i] = i == 0            ? __builtin_huge_val()
+                      : i < kPowExp - 1 ? exp2(hi) * fma(lo, 0.69314718055994530942, 1.0)
+                                        : 0.0;
   }
   for (int k = threadIdx.x; k < kLogTab; k += blockDim.x) {
     const double inv = 1.0 / (1.0 + (k + 0.5) / kLogTab);
@@ -335,20 +355,23 @@ __device__ __forceinline__ void pow_table_init(double nh) {
   }
 }
 
+constexpr double kPowLow = 3.0;
+
+// a >= 0; DEG: the last power of the binomial series (6 for |nh| <= kPowLow, else 10).
+template <int DEG = 10>
 __device__ __forceinline__ double pow_t(double a) {
   const unsigned long long b = __builtin_bit_cast(unsigned long long, a);
   const unsigned int hi = static_cast<unsigned int>(b >> 32);
   const int k = static_cast<int>((hi >> 12) & (kLogTab - 1));
-  const int ei = static_cast<int>((hi >> 20) & 0x7ff);
+  const int ei = static_cast<int>(hi >> 20);
   const double m = __builtin_bit_cast(double, (b & 0x000fffffffffffffull) | 0x3ff0000000000000ull);
   const double2 t = pow_mtable()[k];
   const double r = fma(m, t.x, -1.0);
   const double* c = pow_coef();
-  double q = c[10];
+  double q = c[DEG];
 #pragma unroll
-  for (int j = 9; j >= 0; --j) q = fma(q, r, c[j]);
-  const double res = pow_etable()[ei] * t.y * q;
-  return a >= 0x1p-1022 ? res : __builtin_huge_val();
+  for (int j = DEG - 1; j >= 0; --j) q = fma(q, r, c[j]);
+  return pow_etable()[ei] * t.y * q;
 }
 
 // Coordinate of padding records in the sweeps' LDS tiles: +inf in FP32 (every weight form
@@ -365,7 +388,8 @@ __device__ __forceinline__ double padT<double>() {
 }
 
 // Weight in the sweeps: weight<PM> in FP32; in FP64 the one-step forms for the fast classes.
-template <int PM>
+// DEG: last power of pow_t's series.
+template <int PM, int DEG = 10>
 __device__ __forceinline__ float weight_sweep(float r2, float nhp) {
   return weight<PM>(r2, nhp);
 }
@@ -373,7 +397,7 @@ __device__ __forceinline__ float weight_sweep(float r2, float nhp) {
 template <int PM>
 __device__ __forceinline__ double weight(double r2, double nhp);
 
-template <int PM>
+template <int PM, int DEG = 10>
 __device__ __forceinline__ double weight_sweep(double r2, double nhp) {
   if constexpr (PM == PM_2) {
     return rcp64_w(r2);
@@ -392,7 +416,7 @@ __device__ __forceinline__ double weight_sweep(double r2, double nhp) {
     const double s = rsq64_w(r2);
     return s * s * s * rsq64_w(s);
   } else {  // general p: the tables of pow_t (pow_table_init in the calling kernel)
-    return pow_t(r2);
+    return pow_t<DEG>(r2);
   }
 }
 

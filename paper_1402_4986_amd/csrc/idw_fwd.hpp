@@ -92,7 +92,7 @@ struct KahanSum {
 // blocks, or with TAIL a last block of fewer.  Padding records are never visited, so that no
 // weight of theirs, however small, reaches the denominator.
 template <typename T, int DIM, int PM, int Q, bool DIAG, int UNR, bool KH = false, bool REL = false,
-          bool TAIL = false, bool FULL = false, typename Acc>
+          bool TAIL = false, bool FULL = false, int DEG = 10, typename Acc>
 __device__ __forceinline__ void fwd_tile(const RecTile<T, DIM, kTile>& tl, int64_t jt, int begin, int end,
                                          const T (&qc)[Q][3], const int64_t (&qi)[Q], T nhp,
                                          const T (&sg)[Q], Acc (&num)[Q], Acc (&den)[Q]) {
@@ -107,7 +107,7 @@ __device__ __forceinline__ void fwd_tile(const RecTile<T, DIM, kTile>& tl, int64
       for (int k = 0; k < Q; ++k) {
         T r2 = sqdist<T, DIM>(qc[k], d);
         if constexpr (REL) r2 *= sg[k];
-        T w = weight_sweep<PM>(r2, nhp);
+        T w = weight_sweep<PM, DEG>(r2, nhp);
         if constexpr (DIAG) {
           if (jt + jj == qi[k]) w = T(0);
         }
@@ -133,7 +133,7 @@ __device__ __forceinline__ void fwd_tile(const RecTile<T, DIM, kTile>& tl, int64
       for (int k = 0; k < Q; ++k) {
         T r2 = sqdist<T, DIM>(qc[k], d);
         if constexpr (REL) r2 *= sg[k];
-        T w = weight_sweep<PM>(r2, nhp);
+        T w = weight_sweep<PM, DEG>(r2, nhp);
         if constexpr (DIAG) {
           if (jt + c0 + jj == qi[k]) w = T(0);
         }
@@ -211,6 +211,54 @@ __device__ __forceinline__ void fwd_tile_run(const RecTile<float, DIM, kTile>& t
   }
 }
 
+// Whole 64-record blocks [0, end) in FP64 for the reciprocal weights (p = 2 and 4), without a
+// self pair: four records' reciprocals from one (rcp64_w4).  Bound by FP64 issue: 8 instructions
+// and a quarter of an estimate, about 43 cycles per pair and wave against 51.5.  The next
+// group's records are read ahead.  65,536 x 262,144, per pair and wave: p = 2 53.9 -> 47.8
+// cycles, p = 4 58.7 -> 52.5; 3-D 63.7 -> 57.5 and 68.4 -> 63.
+template <int DIM, int PM, int Q, typename Acc>
+__device__ __forceinline__ void fwd_tile_rcp4(const RecTile<double, DIM, kTile>& tl, int end,
+                                              const double (&qc)[Q][3], Acc (&num)[Q], Acc (&den)[Q]) {
+  static_assert(PM == PM_2 || PM == PM_4, "reciprocal weights");
+  constexpr int CH = 64, G = 4;
+#pragma unroll 1
+  for (int c0 = 0; c0 < end; c0 += CH) {
+    double an[Q], ad[Q];
+#pragma unroll
+    for (int k = 0; k < Q; ++k) an[k] = ad[k] = 0.0;
+    P4<double> d[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) d[g] = tl.get(c0 + g);
+#pragma unroll 2
+    for (int j = 0; j < CH; j += G) {
+      double v[G], w[Q][G];
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        v[g] = DIM == 3 ? d[g].w : d[g].z;
+#pragma unroll
+        for (int k = 0; k < Q; ++k) w[k][g] = sqdist<double, DIM>(qc[k], d[g]);
+      }
+#pragma unroll
+      for (int g = 0; g < G; ++g) d[g] = tl.get(c0 + ((j + G + g) & (CH - 1)));  // the next group
+#pragma unroll
+      for (int k = 0; k < Q; ++k) {
+        rcp64_w4(w[k]);
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          const double t = PM == PM_4 ? w[k][g] * w[k][g] : w[k][g];
+          an[k] = fma(t, v[g], an[k]);
+          ad[k] += t;
+        }
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < Q; ++k) {
+      num[k].add(an[k]);
+      den[k].add(ad[k]);
+    }
+  }
+}
+
 // Finalise one query from its (num, den) in scaled units.
 template <typename T>
 __device__ __forceinline__ void fwd_finish(int64_t i, double num, double den, const double* hdr,
@@ -232,6 +280,13 @@ struct SweepTune {
   static constexpr int UNR = PM == PM_GEN ? 2 : 4;
   static constexpr int WMIN = kF32 ? (Q >= 8 ? 2 : 4) : 1;
   static constexpr int WMAX = kF32 ? WMIN : 8;
+  static constexpr int DEG = 10;  // last power of the FP64 general-p series
+};
+// |p / 2| <= kPowLow (p = 1.7, 65,536 x 262,144: 137 cycles per pair and wave with the series
+// through r^10 and a comparison for zero, 131 without the comparison, 108 through r^6).
+template <int Q>
+struct SweepTuneLow : SweepTune<double, Q, PM_GEN> {
+  static constexpr int DEG = 6;
 };
 
 // REL: relative weights; rmin holds each query's nearest squared distance (FP32 bits,
@@ -320,10 +375,14 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(Tune::WMIN,
       const int whole = cnt & ~63;
       if constexpr (sizeof(T) == 4) {
         fwd_tile_run<DIM, PM, Q, KH, REL>(tl, whole, qc, nhp, sg, nacc, dacc);
+      } else if constexpr (PM == PM_2 || PM == PM_4) {
+        fwd_tile_rcp4<DIM, PM, Q>(tl, whole, qc, nacc, dacc);
       } else if (whole == kTile) {
-        fwd_tile<T, DIM, PM, Q, false, Tune::UNR, KH, REL, false, true>(tl, jt, 0, kTile, qc, qi, nhp, sg, nacc, dacc);
+        fwd_tile<T, DIM, PM, Q, false, Tune::UNR, KH, REL, false, true, Tune::DEG>(tl, jt, 0, kTile, qc, qi, nhp, sg,
+                                                                                   nacc, dacc);
       } else if (whole > 0) {
-        fwd_tile<T, DIM, PM, Q, false, Tune::UNR, KH, REL>(tl, jt, 0, whole, qc, qi, nhp, sg, nacc, dacc);
+        fwd_tile<T, DIM, PM, Q, false, Tune::UNR, KH, REL, false, false, Tune::DEG>(tl, jt, 0, whole, qc, qi, nhp, sg,
+                                                                                    nacc, dacc);
       }
       if (whole < cnt)
         fwd_tile<T, DIM, PM, Q, false, 1, KH, REL, true>(tl, jt, whole, cnt, qc, qi, nhp, sg, nacc, dacc);
@@ -728,6 +787,13 @@ hipError_t launch_fwd_sweep_q(const FwdArgs& a, hipStream_t st) {
         return hipErrorInvalidValue;
     }
   } else {
+    if constexpr (PM == PM_GEN) {
+      if (0.5 * a.p <= kPowLow && Q == 2) {
+        hipLaunchKernelGGL((k_fwd_sweep<T, DIM, L, PM, 2, false, false, SweepTuneLow<2>>), grid, dim3(kWG), 0, st,
+                           IDW_FWD_ARGS);
+        return hipGetLastError();
+      }
+    }
     switch (Q) {
       IDW_FWD_Q(2)
       IDW_FWD_Q(4)

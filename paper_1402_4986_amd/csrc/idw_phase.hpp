@@ -13,9 +13,9 @@
 // on groups of pairs whose transcendentals form one run, and their register budgets are set
 // for an even number of waves per SIMD.
 //
-// Records in LDS: a broadcast ds_read_b128 takes 4 cycles of the CU's LDS, a ds_read_b96 8,
-// so 2-D records are kept as a coordinate pair array and a value array and read four at a
-// time (three ds_read_b128), 3-D records as four floats.
+// Records in LDS: a broadcast ds_read_b128 takes 4 cycles of the CU's LDS, a ds_read_b96 or
+// ds_read2_b64 8, so 2-D records are kept as a coordinate pair array and a value array (FP32
+// read four records at a time, three ds_read_b128), 3-D records as four values.
 #pragma once
 
 #include "idw_device.hpp"
@@ -29,17 +29,17 @@ struct RecTile {
   __device__ __forceinline__ void put(int j, const P4<T>& d) { r[j] = d; }
   __device__ __forceinline__ P4<T> get(int j) const { return r[j]; }
 };
-template <int N>
-struct RecTile<float, 2, N> {
-  alignas(16) P2<float> xy[N];
-  alignas(16) float v[N];
-  __device__ __forceinline__ void put(int j, const P4<float>& d) {
-    xy[j] = P2<float>{d.x, d.y};
+template <typename T, int N>
+struct RecTile<T, 2, N> {
+  alignas(32) P2<T> xy[N];
+  alignas(32) T v[N];
+  __device__ __forceinline__ void put(int j, const P4<T>& d) {
+    xy[j] = P2<T>{d.x, d.y};
     v[j] = d.z;
   }
-  __device__ __forceinline__ P4<float> get(int j) const {
-    const P2<float> c = xy[j];
-    return P4<float>{c.x, c.y, v[j], 0.f};
+  __device__ __forceinline__ P4<T> get(int j) const {
+    const P2<T> c = xy[j];
+    return P4<T>{c.x, c.y, v[j], T(0)};
   }
 };
 
