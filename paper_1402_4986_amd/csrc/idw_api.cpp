@@ -243,20 +243,33 @@ WsPlan plan_workspace(const idw_points* data, const idw_points* query, int preci
     const int64_t gcap = std::min<int64_t>(nqb, std::max<int64_t>(1, kPartBudget / (8 * n)));
     w.fused_groups = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(gcap, cdiv(target, w.fused_ranges))));
   } else if (m > 0) {
-    // about 4096 workgroups of 512 threads (8 rounds of the 512 that are resident), G and the
-    // ranges in the proportion that makes the partials' traffic, G n + 4 R m doubles written and
-    // read back, smallest; ranges of at least 4096 points (between two additions over the
-    // lanes) unless fewer than 1024 workgroups would be left; each array within kPartBudget.
-    const int64_t target = 4096;
-    const int64_t gcap = std::min<int64_t>(cdiv(m, 128), std::max<int64_t>(1, kPartBudget / (8 * n)));
+    // The (groups, ranges) of least estimated time, in tiles (128 queries x 512 points, 9.4 us
+    // with 512 workgroups resident): rounds of 512 workgroups x query blocks per workgroup x
+    // (tiles per range + half a tile to prepare the queries and add over the lanes), the uneven
+    // end of the last round (131,072 x 1M, p = 2: 46.7 cycles a pair in one round, 45.3 in two,
+    // 44.8 in four, 44.0 in eight), and the partials' traffic, G n + 4 R m doubles written and
+    // read back at about 2 TB/s.  Each partial array stays within kPartBudget.
+    const int64_t nqb = cdiv(m, 128);
+    const int64_t gcap = std::min<int64_t>(nqb, std::max<int64_t>(1, kPartBudget / (8 * n)));
     const int64_t rcap = std::min<int64_t>({cdiv(n, kTile), std::max<int64_t>(1, kPartBudget / (32 * m)), 32768});
-    const double even = std::sqrt(4.0 * target * static_cast<double>(m) / static_cast<double>(n));
-    int64_t g = std::min<int64_t>(gcap, std::max<int64_t>(1, std::llround(std::min(even, 1e6))));
-    int64_t r = std::min<int64_t>(rcap, cdiv(target, g));
-    r = std::max<int64_t>(std::min<int64_t>(r, cdiv(n, 4096)), std::min<int64_t>(r, cdiv(1024, g)));
-    w.fused_chunk = cdiv(cdiv(n, r), kTile) * kTile;
-    w.fused_ranges = static_cast<int>(cdiv(n, w.fused_chunk));
-    w.fused_groups = static_cast<int>(std::min<int64_t>(gcap, std::max<int64_t>(g, cdiv(1024, w.fused_ranges))));
+    double best = 0.0;
+    for (int64_t want = 1;; want = std::min<int64_t>(rcap, want < 4 ? want + 1 : want + want / 3)) {
+      const int64_t tiles = cdiv(cdiv(n, want), kTile), r = cdiv(n, tiles * kTile);
+      for (int64_t rounds = 1; rounds <= 16; rounds += rounds < 8 ? 1 : 8) {
+        const int64_t g = std::min<int64_t>(gcap, std::max<int64_t>(1, 512 * rounds / r));
+        const double t = (static_cast<double>(cdiv(g * r, 512)) + 0.1) * static_cast<double>(cdiv(nqb, g)) *
+                             (static_cast<double>(tiles) + 0.5) +
+                         8e-7 * (static_cast<double>(g) * n + 4.0 * r * m);
+        if (best == 0.0 || t < best) {
+          best = t;
+          w.fused_groups = static_cast<int>(g);
+          w.fused_ranges = static_cast<int>(r);
+          w.fused_chunk = tiles * kTile;
+        }
+        if (g == gcap) break;
+      }
+      if (want >= rcap) break;
+    }
   }
   w.nbbox = static_cast<int>(std::min<int64_t>(1024, cdiv(n, kWG)));
   w.nwg_dp = static_cast<int>(cdiv(m, kWG));

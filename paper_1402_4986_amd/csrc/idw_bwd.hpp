@@ -422,7 +422,8 @@ __device__ __forceinline__ void bwd_qmerge_block(int64_t block, const double4* _
     const double D = saved_den[i];
     if (route[i] == F_FP32) {  // the others come from the FP64 fix-up
       double P[2] = {0.0, 0.0}, G[3][2] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};
-      for (int c = 0; c < split; ++c) {
+#pragma unroll 4
+      for (int c = 0; c < split; ++c) {  // unrolled: several rows' loads in flight
         const double4 v = part[static_cast<int64_t>(c) * m + i];
         two_sum_acc(P[0], P[1], v.x);
         two_sum_acc(G[0][0], G[0][1], v.y);
@@ -609,6 +610,7 @@ __device__ __forceinline__ void bwd_zmerge_block(int64_t block, const double* __
   const int64_t j = block * kWG + threadIdx.x;
   if (j >= n) return;
   double h = 0.0, l = 0.0;
+#pragma unroll 8
   for (int c = 0; c < split; ++c) two_sum_acc(h, l, part[static_cast<int64_t>(c) * n + j]);
   grad_z[j] = static_cast<T>(h + l);
 }
@@ -780,6 +782,7 @@ __device__ __forceinline__ void bwd_xmerge_block(int64_t block, const double* __
   const int64_t t = block * kWG + threadIdx.x;
   if (t >= n * DIM) return;
   double h = 0.0, l = 0.0;
+#pragma unroll 8
   for (int c = 0; c < split; ++c) two_sum_acc(h, l, part[static_cast<int64_t>(c) * n * DIM + t]);
   grad_x[t] = static_cast<T>(p * hdr[H_SCALE] * (h + l));
 }
