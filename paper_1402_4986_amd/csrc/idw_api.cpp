@@ -685,9 +685,11 @@ static int forward_impl(const idw_points* data, const idw_points* query, double 
     return rc;
   if ((rc = check_hip(timed(IDW_T_FWD_SWEEP, st, [&] { return F.fwd_sweep(a, f64, st); }), "forward sweep")))
     return rc;
-  if ((rc = check_hip(merge_split(a, route_args(m, ws, w), f64, st), "merge"))) return rc;
-  if ((rc = check_hip(settle_routes(F, data, query, f64, excl, ws, w, st), "near-coincidence check")))
-    return rc;
+  a.small = small_call(a.n, m);
+  if (!a.small) {
+    if ((rc = check_hip(merge_split(a, route_args(m, ws, w), f64, st), "merge"))) return rc;
+    if ((rc = check_hip(settle_routes(F, data, query, f64, excl, ws, w, st), "near-coincidence check"))) return rc;
+  }
   if ((rc = check_hip(F.fwd_fixup(a, f64, st), "FP64 fix-up"))) return rc;
   return IDW_OK;
 }
@@ -769,6 +771,8 @@ int idw_backward(const idw_points* data, const idw_points* query, double p, int3
   a.grad_x = ndx ? grad_x : nullptr;
   a.part_x = ndx ? reinterpret_cast<double*>(ws + w.part_x) : nullptr;
   a.wg_dp = ndp ? reinterpret_cast<double*>(ws + w.wg_dp) : nullptr;
+  a.nwg_dp = w.nwg_dp;
+  a.grad_p = ndp ? grad_p : nullptr;
   a.list = reinterpret_cast<const int*>(ws + w.list);
   a.count = reinterpret_cast<const int*>(ws + w.hdr + 256);
   a.slot_coef = reinterpret_cast<double*>(ws + w.slot_coef);
@@ -820,8 +824,6 @@ int idw_backward(const idw_points* data, const idw_points* query, double p, int3
     if ((rc = check_hip(bwd_merge(a, ndp || ndq, ndz, ndx, f64, st), "merge"))) return rc;
   }
   if ((rc = check_hip(F.bwd_fixup(a, f64, st), "FP64 fix-up"))) return rc;
-  if (ndp && (rc = check_hip(dp_final(a.wg_dp, w.nwg_dp, a.slot_dp, a.count, grad_p, st), "dp reduction")))
-    return rc;
   return IDW_OK;
 }
 

@@ -806,6 +806,20 @@ __global__ __launch_bounds__(kWG) void k_bwd_merge(unsigned nq, unsigned nz, con
     bwd_xmerge_block<T, DIM>(blockIdx.x - nq - nz, part_x, n, split_z, p, hdr, grad_x);
 }
 
+// dp = sum of the sweep workgroups' partials (in workgroup order) plus the FP64 fix-up slots'
+// partials (in ascending query order), by one workgroup in a fixed-order tree.
+__device__ __forceinline__ void dp_final_block(const double* __restrict__ wg_dp, int nwg,
+                                               const double* __restrict__ slot_dp, int cnt,
+                                               double* __restrict__ grad_p) {
+  __shared__ double red[kWG];
+  const int t = threadIdx.x;
+  double h = 0.0, l = 0.0;
+  for (int b = t; b < nwg; b += kWG) two_sum_acc(h, l, wg_dp[b]);
+  for (int b = t; b < cnt; b += kWG) two_sum_acc(h, l, slot_dp[b]);
+  const double tot = block_sum(h, red) + block_sum(l, red);
+  if (t == 0) *grad_p = tot;
+}
+
 // FP64 fix-up of the adjoint for flagged queries (exact hits and near-coincident points),
 // in two passes over the data, each cut into chunks as in k_fwd_fixup:
 //   pass 1: D, Z and the hit count of each flagged query;
@@ -834,17 +848,74 @@ __device__ __forceinline__ void bwd_fix1_finish(int sl, int64_t i, double num, d
   }
 }
 
+template <typename T>
+__device__ __forceinline__ void bwd_fix2_finish(int sl, int64_t i, const double4& s, int dim, double p, double D,
+                                                const T* __restrict__ grad_out, T* __restrict__ grad_q,
+                                                double* __restrict__ slot_dp) {
+  const double g = static_cast<double>(grad_out[i]);
+  const double G[3] = {s.y, s.z, s.w};
+  slot_dp[sl] = -(g / D) * s.x;
+  if (grad_q)
+    for (int d = 0; d < dim; ++d) grad_q[i * dim + d] = static_cast<T>(-(p * g / D) * G[d]);
+}
+
+// P and G of query i over data points [j0, j1) in FP64, over the workgroup (as fix_query).
+template <typename T, int DIM, int L, int PM>
+__device__ __forceinline__ double4 fix_query_grad(const DevPts& data, const DevPts& query, int64_t i, int64_t j0,
+                                                  int64_t j1, double Z, bool excl, double nhp,
+                                                  double4 (&red)[kWaves]) {
+  T qt[3] = {T(0), T(0), T(0)};
+  Loader<T, DIM, L>::query(query, i, qt);
+  NSum P, G[3];
+  for (int64_t j = j0 + threadIdx.x; j < j1; j += kWG) {
+    if (excl && j == i) continue;
+    T cc[3] = {T(0), T(0), T(0)}, v;
+    Loader<T, DIM, L>::data(data, j, cc, v);
+    double e[3] = {0.0, 0.0, 0.0}, r2 = 0.0;
+#pragma unroll
+    for (int d = 0; d < DIM; ++d) {
+      e[d] = static_cast<double>(qt[d]) - static_cast<double>(cc[d]);
+      r2 += e[d] * e[d];
+    }
+    const double wgt = weight<PM>(r2, nhp);
+    const double cz = static_cast<double>(v) - Z;
+    P.add(wgt * 0.5 * log(r2) * cz);
+    const double u = (wgt / r2) * cz;
+#pragma unroll
+    for (int d = 0; d < DIM; ++d) G[d].add(u * e[d]);
+  }
+  double v[4] = {P.value(), G[0].value(), G[1].value(), G[2].value()};
+#pragma unroll
+  for (int k = 0; k < 1 + DIM; ++k)
+#pragma unroll
+    for (int x = 1; x < 64; x <<= 1) v[k] += __shfl_xor(v[k], x);
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = make_double4(v[0], v[1], v[2], v[3]);
+  __syncthreads();
+  double4 s = red[0];
+#pragma unroll
+  for (int w = 1; w < kWaves; ++w) {
+    s.x += red[w].x;
+    s.y += red[w].y;
+    s.z += red[w].z;
+    s.w += red[w].w;
+  }
+  return s;
+}
+
+// With `both` (dp or dq requested) a query that one workgroup holds whole (C == 1) goes on to the
+// second pass at once, and k_bwd_fix2 leaves it alone.
 template <typename T, int DIM, int L, int PM>
 __global__ __launch_bounds__(kWG) void k_bwd_fix1(DevPts data, int64_t n, DevPts query, double p,
                                                   unsigned flags, const int* __restrict__ list,
-                                                  const int* __restrict__ count, int cmax,
+                                                  const int* __restrict__ count, int cmax, int both,
                                                   double4* __restrict__ fpart,
                                                   const T* __restrict__ grad_out, T* __restrict__ grad_q,
                                                   double* __restrict__ slot_coef, int* __restrict__ slot_hits,
                                                   double* __restrict__ slot_dp, double* __restrict__ slot_z,
                                                   double* __restrict__ slot_den) {
-  __shared__ double red[kWG];
-  __shared__ long long redi[kWG];
+  __shared__ FixSums red[kWaves];
+  __shared__ double4 redg[kWaves];
   const int cnt = *count;
   const int C = fix_chunks(cnt, cmax);
   const int64_t total = static_cast<int64_t>(cnt) * C;
@@ -853,41 +924,20 @@ __global__ __launch_bounds__(kWG) void k_bwd_fix1(DevPts data, int64_t n, DevPts
   const double nhp = -0.5 * p;
   for (int64_t w = blockIdx.x; w < total; w += gridDim.x) {
     const int sl = static_cast<int>(w / C);
-    const int64_t c = w % C;
     const int64_t i = list[sl];
-    const int64_t j0 = c * len;
+    const int64_t j0 = (w % C) * len;
     const int64_t j1 = (j0 + len < n) ? j0 + len : n;
-    T qt[3] = {T(0), T(0), T(0)};
-    Loader<T, DIM, L>::query(query, i, qt);
-    NSum num, den;
-    long long h = 0;
-    for (int64_t j = j0 + threadIdx.x; j < j1; j += kWG) {
-      if (excl && j == i) continue;
-      T cc[3] = {T(0), T(0), T(0)}, v;
-      Loader<T, DIM, L>::data(data, j, cc, v);
-      double r2 = 0.0;
-#pragma unroll
-      for (int d = 0; d < DIM; ++d) {
-        const double e = static_cast<double>(qt[d]) - static_cast<double>(cc[d]);
-        r2 += e * e;
-      }
-      if (r2 == 0.0) {
-        ++h;
-      } else {
-        const double wgt = weight<PM>(r2, nhp);
-        num.add(wgt * static_cast<double>(v));
-        den.add(wgt);
-      }
+    const FixSums s = fix_query<T, DIM, L, PM>(data, query, i, j0, j1, excl, nhp, red);
+    if (C > 1) {
+      if (threadIdx.x == 0) fpart[w] = make_double4(s.num, s.den, 0.0, static_cast<double>(s.h));
+      continue;
     }
-    const double tn = block_sum(num.value(), red);
-    const double td = block_sum(den.value(), red);
-    const long long th = block_sum_i64(h, redi);
-    if (threadIdx.x == 0) {
-      if (C == 1)
-        bwd_fix1_finish<T>(sl, i, tn, td, static_cast<double>(th), DIM, grad_out, grad_q, slot_coef,
-                           slot_hits, slot_dp, slot_z, slot_den);
-      else
-        fpart[w] = make_double4(tn, td, 0.0, static_cast<double>(th));
+    if (threadIdx.x == 0)
+      bwd_fix1_finish<T>(sl, i, s.num, s.den, static_cast<double>(s.h), DIM, grad_out, grad_q, slot_coef, slot_hits,
+                         slot_dp, slot_z, slot_den);
+    if (both && s.h == 0) {
+      const double4 g = fix_query_grad<T, DIM, L, PM>(data, query, i, j0, j1, s.num / s.den, excl, nhp, redg);
+      if (threadIdx.x == 0) bwd_fix2_finish<T>(sl, i, g, DIM, p, s.den, grad_out, grad_q, slot_dp);
     }
   }
 }
@@ -919,73 +969,28 @@ __global__ __launch_bounds__(kWG) void k_bwd_fix1_merge(const int* __restrict__ 
   }
 }
 
-template <typename T>
-__device__ __forceinline__ void bwd_fix2_finish(int sl, int64_t i, double P, const double (&G)[3], int dim,
-                                                double p, const T* __restrict__ grad_out,
-                                                T* __restrict__ grad_q, double* __restrict__ slot_dp,
-                                                const double* __restrict__ slot_den) {
-  const double g = static_cast<double>(grad_out[i]);
-  const double D = slot_den[sl];
-  slot_dp[sl] = -(g / D) * P;
-  if (grad_q)
-    for (int d = 0; d < dim; ++d) grad_q[i * dim + d] = static_cast<T>(-(p * g / D) * G[d]);
-}
-
 template <typename T, int DIM, int L, int PM>
 __global__ __launch_bounds__(kWG) void k_bwd_fix2(DevPts data, int64_t n, DevPts query, double p,
                                                   unsigned flags, const int* __restrict__ list,
                                                   const int* __restrict__ count, int cmax,
                                                   double4* __restrict__ fpart,
-                                                  const T* __restrict__ grad_out, T* __restrict__ grad_q,
                                                   const int* __restrict__ slot_hits,
-                                                  double* __restrict__ slot_dp,
-                                                  const double* __restrict__ slot_z,
-                                                  const double* __restrict__ slot_den) {
-  __shared__ double red[kWG];
+                                                  const double* __restrict__ slot_z) {
+  __shared__ double4 redg[kWaves];
   const int cnt = *count;
   const int C = fix_chunks(cnt, cmax);
+  if (C <= 1) return;  // done by k_bwd_fix1
   const int64_t total = static_cast<int64_t>(cnt) * C;
-  const int64_t len = C > 0 ? (n + C - 1) / C : 0;
+  const int64_t len = (n + C - 1) / C;
   const bool excl = (flags & 1u) != 0;
   const double nhp = -0.5 * p;
   for (int64_t w = blockIdx.x; w < total; w += gridDim.x) {
     const int sl = static_cast<int>(w / C);
     if (slot_hits[sl] > 0) continue;  // uniform over the workgroup
-    const int64_t c = w % C;
-    const int64_t i = list[sl];
-    const int64_t j0 = c * len;
+    const int64_t j0 = (w % C) * len;
     const int64_t j1 = (j0 + len < n) ? j0 + len : n;
-    const double Z = slot_z[sl];
-    T qt[3] = {T(0), T(0), T(0)};
-    Loader<T, DIM, L>::query(query, i, qt);
-    const double q[3] = {static_cast<double>(qt[0]), static_cast<double>(qt[1]), static_cast<double>(qt[2])};
-    NSum P, G[3];
-    for (int64_t j = j0 + threadIdx.x; j < j1; j += kWG) {
-      if (excl && j == i) continue;
-      T cc[3] = {T(0), T(0), T(0)}, v;
-      Loader<T, DIM, L>::data(data, j, cc, v);
-      double e[3] = {0.0, 0.0, 0.0}, r2 = 0.0;
-#pragma unroll
-      for (int d = 0; d < DIM; ++d) {
-        e[d] = q[d] - static_cast<double>(cc[d]);
-        r2 += e[d] * e[d];
-      }
-      const double wgt = weight<PM>(r2, nhp);
-      const double cz = static_cast<double>(v) - Z;
-      P.add(wgt * 0.5 * log(r2) * cz);
-      const double u = (wgt / r2) * cz;
-#pragma unroll
-      for (int d = 0; d < DIM; ++d) G[d].add(u * e[d]);
-    }
-    const double tP = block_sum(P.value(), red);
-    double tG[3] = {0.0, 0.0, 0.0};
-    for (int d = 0; d < DIM; ++d) tG[d] = block_sum(G[d].value(), red);
-    if (threadIdx.x == 0) {
-      if (C == 1)
-        bwd_fix2_finish<T>(sl, i, tP, tG, DIM, p, grad_out, grad_q, slot_dp, slot_den);
-      else
-        fpart[w] = make_double4(tP, tG[0], tG[1], tG[2]);
-    }
+    const double4 g = fix_query_grad<T, DIM, L, PM>(data, query, list[sl], j0, j1, slot_z[sl], excl, nhp, redg);
+    if (threadIdx.x == 0) fpart[w] = g;
   }
 }
 
@@ -1011,8 +1016,9 @@ __global__ __launch_bounds__(kWG) void k_bwd_fix2_merge(const int* __restrict__ 
       two_sum_acc(G[1][0], G[1][1], v.z);
       two_sum_acc(G[2][0], G[2][1], v.w);
     }
-    const double g3[3] = {G[0][0] + G[0][1], G[1][0] + G[1][1], G[2][0] + G[2][1]};
-    bwd_fix2_finish<T>(sl, list[sl], P[0] + P[1], g3, DIM, p, grad_out, grad_q, slot_dp, slot_den);
+    bwd_fix2_finish<T>(sl, list[sl],
+                       make_double4(P[0] + P[1], G[0][0] + G[0][1], G[1][0] + G[1][1], G[2][0] + G[2][1]), DIM, p,
+                       slot_den[sl], grad_out, grad_q, slot_dp);
   }
 }
 
@@ -1026,8 +1032,15 @@ __global__ __launch_bounds__(kWG) void k_bwd_fixz(DevPts data, int64_t n, DevPts
                                                   const double* __restrict__ slot_coef,
                                                   const int* __restrict__ slot_hits,
                                                   const double* __restrict__ slot_z,
-                                                  T* __restrict__ grad_z, T* __restrict__ grad_x) {
+                                                  T* __restrict__ grad_z, T* __restrict__ grad_x,
+                                                  const double* __restrict__ wg_dp, int nwg,
+                                                  const double* __restrict__ slot_dp,
+                                                  double* __restrict__ grad_p) {
   const int cnt = *count;
+  if (grad_p && blockIdx.x == gridDim.x - 1) {  // the last workgroup reduces dp instead
+    dp_final_block(wg_dp, nwg, slot_dp, cnt, grad_p);
+    return;
+  }
   if (cnt == 0) return;
   const int64_t j = static_cast<int64_t>(blockIdx.x) * kWG + threadIdx.x;
   if (j >= n) return;
@@ -1111,23 +1124,28 @@ template <typename T, int DIM, int L, int PM>
 hipError_t launch_bwd_fix_t(const BwdArgs& a, hipStream_t st) {
   const T* go = static_cast<const T*>(a.grad_out);
   T* gq = static_cast<T*>(a.grad_q);
+  const int both = (a.flags & 0xcu) != 0 ? 1 : 0;  // dp or dq requested
   hipLaunchKernelGGL((k_bwd_fix1<T, DIM, L, PM>), dim3(kFixGrid), dim3(kWG), 0, st, a.data, a.n, a.query,
-                     a.p, a.flags, a.list, a.count, a.fix_cmax, a.fpart, go, gq, a.slot_coef, a.slot_hits,
+                     a.p, a.flags, a.list, a.count, a.fix_cmax, both, a.fpart, go, gq, a.slot_coef, a.slot_hits,
                      a.slot_dp, a.slot_z, a.slot_den);
-  hipLaunchKernelGGL((k_bwd_fix1_merge<T, DIM>), dim3(4), dim3(kWG), 0, st, a.list, a.count, a.fix_cmax,
-                     a.fpart, go, gq, a.slot_coef, a.slot_hits, a.slot_dp, a.slot_z, a.slot_den);
-  if (a.flags & 0xcu) {  // dp or dq requested
-    hipLaunchKernelGGL((k_bwd_fix2<T, DIM, L, PM>), dim3(kFixGrid), dim3(kWG), 0, st, a.data, a.n, a.query,
-                       a.p, a.flags, a.list, a.count, a.fix_cmax, a.fpart, go, gq, a.slot_hits, a.slot_dp,
-                       a.slot_z, a.slot_den);
-    hipLaunchKernelGGL((k_bwd_fix2_merge<T, DIM>), dim3(4), dim3(kWG), 0, st, a.list, a.count, a.fix_cmax,
-                       a.fpart, a.p, go, gq, a.slot_hits, a.slot_dp, a.slot_den);
+  if (a.fix_cmax > 1) {  // queries whose data range may be cut into chunks
+    hipLaunchKernelGGL((k_bwd_fix1_merge<T, DIM>), dim3(4), dim3(kWG), 0, st, a.list, a.count, a.fix_cmax,
+                       a.fpart, go, gq, a.slot_coef, a.slot_hits, a.slot_dp, a.slot_z, a.slot_den);
+    if (both) {
+      hipLaunchKernelGGL((k_bwd_fix2<T, DIM, L, PM>), dim3(kFixGrid), dim3(kWG), 0, st, a.data, a.n, a.query,
+                         a.p, a.flags, a.list, a.count, a.fix_cmax, a.fpart, a.slot_hits, a.slot_z);
+      hipLaunchKernelGGL((k_bwd_fix2_merge<T, DIM>), dim3(4), dim3(kWG), 0, st, a.list, a.count, a.fix_cmax,
+                         a.fpart, a.p, go, gq, a.slot_hits, a.slot_dp, a.slot_den);
+    }
   }
-  if (a.grad_z || a.grad_x)
+  if (a.grad_z || a.grad_x)  // and dp, by one more workgroup
     hipLaunchKernelGGL((k_bwd_fixz<T, DIM, L, PM>),
-                       dim3(static_cast<unsigned>((a.n + kWG - 1) / kWG)), dim3(kWG), 0, st,
+                       dim3(static_cast<unsigned>((a.n + kWG - 1) / kWG) + (a.grad_p ? 1u : 0u)), dim3(kWG), 0, st,
                        a.data, a.n, a.query, a.p, a.flags, a.list, a.count, a.slot_coef,
-                       a.slot_hits, a.slot_z, static_cast<T*>(a.grad_z), static_cast<T*>(a.grad_x));
+                       a.slot_hits, a.slot_z, static_cast<T*>(a.grad_z), static_cast<T*>(a.grad_x), a.wg_dp, a.nwg_dp,
+                       a.slot_dp, a.grad_p);
+  else if (a.grad_p)
+    return dp_final(a.wg_dp, a.nwg_dp, a.slot_dp, a.count, a.grad_p, st);
   return hipGetLastError();
 }
 

@@ -10,51 +10,41 @@
 namespace idw {
 
 // Reduces the per-workgroup extent partials and fills the workspace header.
-__global__ __launch_bounds__(kWG) void k_bbox_final(const double* __restrict__ part, int nb,
-                                                    int dim, double p, int f32s, int rel,
-                                                    double* __restrict__ hdr) {
-  __shared__ double red[kWG];
-  __shared__ double bmn[3], bmx[3];
-  const int t = threadIdx.x;
-  for (int d = 0; d < dim; ++d) {
-    double mn = __builtin_huge_val(), mx = -__builtin_huge_val();
-    for (int b = t; b < nb; b += kWG) {
-      mn = fmin(mn, part[b * kBboxStride + d]);
-      mx = fmax(mx, part[b * kBboxStride + 3 + d]);
+template <int DIM>
+__global__ __launch_bounds__(kWG) void k_bbox_final(const double* __restrict__ part, int nb, double p, int f32s,
+                                                    int rel, double* __restrict__ hdr) {
+  __shared__ double red[kWG / 64][Box<double, DIM>::N];
+  Box<double, DIM> b;
+  b.clear();
+  for (int k = threadIdx.x; k < nb; k += kWG) {
+    const double* o = part + k * kBboxStride;
+#pragma unroll
+    for (int d = 0; d < DIM; ++d) {
+      b.v[d] = fmax(b.v[d], -o[d]);
+      b.v[DIM + d] = fmax(b.v[DIM + d], o[3 + d]);
     }
-    for (int pass = 0; pass < 2; ++pass) {
-      red[t] = pass ? mx : mn;
-      __syncthreads();
-      for (int s = kWG / 2; s > 0; s >>= 1) {
-        if (t < s) red[t] = pass ? fmax(red[t], red[t + s]) : fmin(red[t], red[t + s]);
-        __syncthreads();
-      }
-      if (pass)
-        mx = red[0];
-      else
-        mn = red[0];
-      __syncthreads();
-    }
-    if (t == 0) {
-      bmn[d] = mn;
-      bmx[d] = mx;
-    }
+    b.v[2 * DIM] = fmax(b.v[2 * DIM], o[6]);
   }
-  double vm = 0.0;
-  for (int b = t; b < nb; b += kWG) vm = fmax(vm, part[b * kBboxStride + 6]);
-  red[t] = vm;
-  __syncthreads();
-  for (int s = kWG / 2; s > 0; s >>= 1) {
-    if (t < s) red[t] = fmax(red[t], red[t + s]);
-    __syncthreads();
+  b.template reduce<kWG>(red);
+  if (threadIdx.x == 0) {
+    double mn[3] = {0.0, 0.0, 0.0}, mx[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int d = 0; d < DIM; ++d) {
+      mn[d] = -b.v[d];
+      mx[d] = b.v[DIM + d];
+    }
+    finish_header(hdr, mn, mx, DIM, b.v[2 * DIM], p, f32s != 0, rel != 0);
   }
-  if (t == 0) finish_header(hdr, bmn, bmx, dim, red[0], p, f32s != 0, rel != 0);
 }
 
 hipError_t bbox_final(const double* part, int nblocks, int dim, double p, bool f32_scaling,
                       bool rel, double* hdr, hipStream_t st) {
-  hipLaunchKernelGGL(k_bbox_final, dim3(1), dim3(kWG), 0, st, part, nblocks, dim, p,
-                     f32_scaling ? 1 : 0, rel ? 1 : 0, hdr);
+  if (dim == 3)
+    hipLaunchKernelGGL(k_bbox_final<3>, dim3(1), dim3(kWG), 0, st, part, nblocks, p, f32_scaling ? 1 : 0, rel ? 1 : 0,
+                       hdr);
+  else
+    hipLaunchKernelGGL(k_bbox_final<2>, dim3(1), dim3(kWG), 0, st, part, nblocks, p, f32_scaling ? 1 : 0, rel ? 1 : 0,
+                       hdr);
   return hipGetLastError();
 }
 
@@ -370,20 +360,11 @@ hipError_t compact_flags(const uint8_t* flag, int64_t m, int* bcnt, int* list, i
   return hipGetLastError();
 }
 
-// dp = sum of the sweep workgroups' partials (in workgroup order) plus the FP64 fix-up
-// slots' partials (in ascending query order).  Single workgroup, fixed-order tree.
 __global__ __launch_bounds__(kWG) void k_dp_final(const double* __restrict__ wg_dp, int nwg,
                                                   const double* __restrict__ slot_dp,
                                                   const int* __restrict__ count,
                                                   double* __restrict__ grad_p) {
-  __shared__ double red[kWG];
-  const int t = threadIdx.x;
-  double h = 0.0, l = 0.0;
-  for (int b = t; b < nwg; b += kWG) two_sum_acc(h, l, wg_dp[b]);
-  const int cnt = *count;
-  for (int b = t; b < cnt; b += kWG) two_sum_acc(h, l, slot_dp[b]);
-  const double tot = block_sum(h, red) + block_sum(l, red);
-  if (t == 0) *grad_p = tot;
+  dp_final_block(wg_dp, nwg, slot_dp, *count, grad_p);
 }
 
 // ---- grid of the nearest-distance searches: geometry and gates, scan of the counts ----

@@ -562,6 +562,73 @@ __device__ __forceinline__ int fix_chunks(int cnt, int cmax) {
   return c < 1 ? 1 : c;
 }
 
+constexpr int kWaves = kWG / 64;
+
+// Sums over data points [j0, j1) of query i in FP64, over the workgroup; every thread gets the
+// totals.  Call uniformly.
+struct FixSums {
+  double num, den, hz;
+  long long h;
+};
+template <typename T, int DIM, int L, int PM>
+__device__ __forceinline__ FixSums fix_query(const DevPts& data, const DevPts& query, int64_t i, int64_t j0, int64_t j1,
+                                             bool excl, double nhp, FixSums (&red)[kWaves]) {
+  T qt[3] = {T(0), T(0), T(0)};
+  Loader<T, DIM, L>::query(query, i, qt);
+  NSum num, den;
+  double hz = 0.0;
+  long long h = 0;
+  for (int64_t j = j0 + threadIdx.x; j < j1; j += kWG) {
+    if (excl && j == i) continue;
+    T cc[3] = {T(0), T(0), T(0)}, v;
+    Loader<T, DIM, L>::data(data, j, cc, v);
+    double r2 = 0.0;
+#pragma unroll
+    for (int d = 0; d < DIM; ++d) {
+      const double e = static_cast<double>(qt[d]) - static_cast<double>(cc[d]);
+      r2 += e * e;
+    }
+    if (r2 == 0.0) {
+      ++h;
+      hz += static_cast<double>(v);
+    } else {
+      const double wgt = weight<PM>(r2, nhp);
+      num.add(wgt * static_cast<double>(v));
+      den.add(wgt);
+    }
+  }
+  // a tree over the lanes of each wave, then the waves in order: two barriers, where four
+  // block_sum()s have 40
+  FixSums s = {num.value(), den.value(), hz, h};
+#pragma unroll
+  for (int x = 1; x < 64; x <<= 1) {
+    s.num += __shfl_xor(s.num, x);
+    s.den += __shfl_xor(s.den, x);
+    s.hz += __shfl_xor(s.hz, x);
+    s.h += __shfl_xor(s.h, x);
+  }
+  __syncthreads();  // the last call's totals are read
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+  __syncthreads();
+  s = red[0];
+#pragma unroll
+  for (int w = 1; w < kWaves; ++w) {
+    s.num += red[w].num;
+    s.den += red[w].den;
+    s.hz += red[w].hz;
+    s.h += red[w].h;
+  }
+  return s;
+}
+
+template <typename T>
+__device__ __forceinline__ void fix_write(const FixSums& s, int64_t i, T* __restrict__ out_z,
+                                          double* __restrict__ out_den) {
+  const double Z = s.h > 0 ? s.hz / static_cast<double>(s.h) : s.num / s.den;
+  out_z[i] = static_cast<T>(Z);
+  if (out_den) out_den[i] = s.h > 0 ? __builtin_huge_val() : s.den;
+}
+
 template <typename T, int DIM, int L, int PM>
 __global__ __launch_bounds__(kWG) void k_fwd_fixup(DevPts data, int64_t n, DevPts query,
                                                    double nhp, unsigned flags,
@@ -570,57 +637,114 @@ __global__ __launch_bounds__(kWG) void k_fwd_fixup(DevPts data, int64_t n, DevPt
                                                    double4* __restrict__ fpart,
                                                    T* __restrict__ out_z,
                                                    double* __restrict__ out_den) {
-  __shared__ double red[kWG];
-  __shared__ long long redi[kWG];
+  __shared__ FixSums red[kWaves];
   const int cnt = *count;
   const int C = fix_chunks(cnt, cmax);
   const int64_t total = static_cast<int64_t>(cnt) * C;
   const int64_t len = C > 0 ? (n + C - 1) / C : 0;
   const bool excl = (flags & 1u) != 0;
   for (int64_t w = blockIdx.x; w < total; w += gridDim.x) {
-    const int sl = static_cast<int>(w / C);
-    const int64_t c = w % C;
-    const int64_t i = list[sl];
-    const int64_t j0 = c * len;
+    const int64_t i = list[w / C];
+    const int64_t j0 = (w % C) * len;
     const int64_t j1 = (j0 + len < n) ? j0 + len : n;
-    T qt[3] = {T(0), T(0), T(0)};
-    Loader<T, DIM, L>::query(query, i, qt);
-    NSum num, den;
-    double hz = 0.0;
-    long long h = 0;
-    for (int64_t j = j0 + threadIdx.x; j < j1; j += kWG) {
-      if (excl && j == i) continue;
-      T cc[3] = {T(0), T(0), T(0)}, v;
-      Loader<T, DIM, L>::data(data, j, cc, v);
-      double r2 = 0.0;
-#pragma unroll
-      for (int d = 0; d < DIM; ++d) {
-        const double e = static_cast<double>(qt[d]) - static_cast<double>(cc[d]);
-        r2 += e * e;
-      }
-      if (r2 == 0.0) {
-        ++h;
-        hz += static_cast<double>(v);
-      } else {
-        const double wgt = weight<PM>(r2, nhp);
-        num.add(wgt * static_cast<double>(v));
-        den.add(wgt);
-      }
-    }
-    const double tn = block_sum(num.value(), red);
-    const double td = block_sum(den.value(), red);
-    const double thz = block_sum(hz, red);
-    const long long th = block_sum_i64(h, redi);
+    const FixSums s = fix_query<T, DIM, L, PM>(data, query, i, j0, j1, excl, nhp, red);
     if (threadIdx.x == 0) {
-      if (C == 1) {
-        const double Z = th > 0 ? thz / static_cast<double>(th) : tn / td;
-        out_z[i] = static_cast<T>(Z);
-        if (out_den) out_den[i] = th > 0 ? __builtin_huge_val() : td;
-      } else {
-        fpart[w] = make_double4(tn, td, thz, static_cast<double>(th));
-      }
+      if (C == 1)
+        fix_write<T>(s, i, out_z, out_den);
+      else
+        fpart[w] = make_double4(s.num, s.den, s.hz, static_cast<double>(s.h));
     }
   }
+}
+
+// Everything after the sweep of a small forward (small_call) in one launch: a wave merges its
+// query's partials (lane c takes chunks c, c + 64, ..., then a fixed tree over the lanes) and
+// finds the route; the workgroup then settles its candidates by their nearest distance and
+// recomputes the queries routed to FP64, one at a time.  Such a call is mostly launches: with
+// this kernel in place of five (merge, nearest-distance check, settling, fix-up and its merge) a
+// call of 1,024 x 1,000 takes 13.5 us in place of 28.7, one of 4,096 x 4,099 20 in place of 32.
+
+template <typename T, int DIM, int L, int PM>
+__global__ __launch_bounds__(kWG) void k_fwd_finish_small(DevPts data, int64_t n, DevPts query, int64_t m, int split,
+                                                          double nhp, unsigned flags,
+                                                          const double* __restrict__ hdr,
+                                                          const double2* __restrict__ part, T* __restrict__ out_z,
+                                                          double* __restrict__ out_den,
+                                                          const uint8_t* __restrict__ route,
+                                                          int* __restrict__ count) {
+  __shared__ FixSums red[kWaves];
+  __shared__ uint8_t routes[kWaves];
+  __shared__ T mins[kWaves];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const bool excl = (flags & 1u) != 0;
+  const int64_t first = static_cast<int64_t>(blockIdx.x) * kWaves;
+  const int64_t i = first + wave;
+  uint8_t r = F_FP32;
+  if (i < m) {
+    if (split > 1) {
+      double nh = 0.0, nl = 0.0, dh = 0.0, dl = 0.0;
+      for (int c = lane; c < split; c += 64) {
+        const double2 v = part[static_cast<int64_t>(c) * m + i];
+        two_sum_acc(nh, nl, v.x);
+        two_sum_acc(dh, dl, v.y);
+      }
+#pragma unroll
+      for (int x = 1; x < 64; x <<= 1) {
+        const double a = __shfl_xor(nh, x), b = __shfl_xor(nl, x), c = __shfl_xor(dh, x), d = __shfl_xor(dl, x);
+        two_sum_acc(nh, nl, a);
+        two_sum_acc(dh, dl, c);
+        nl += b;
+        dl += d;
+      }
+      const double num = nh + nl, den = dh + dl;
+      r = route_of(den, hdr, false);
+      if (lane == 0) {
+        out_z[i] = static_cast<T>(num / den);
+        if (out_den) out_den[i] = den * hdr[H_DEN_UNIT];
+      }
+    } else {
+      r = route[i];  // the sweep has finalised
+    }
+  }
+  if (lane == 0) routes[wave] = r;
+  if (!__syncthreads_or(lane == 0 && r != F_FP32)) return;
+  int fixed = 0;
+  for (int k = 0; k < kWaves; ++k) {  // uniform over the workgroup
+    uint8_t rk = routes[k];
+    const int64_t q = first + k;
+    if (rk == F_CANDIDATE) {
+      const T s = static_cast<T>(hdr[H_SCALE]);
+      T c[3] = {T(0), T(0), T(0)};
+      Loader<T, DIM, L>::query(query, q, c);
+#pragma unroll
+      for (int d = 0; d < 3; ++d) c[d] *= s;
+      T mn = infT<T>();
+      for (int64_t j = threadIdx.x; j < n; j += kWG) {
+        T x[3] = {T(0), T(0), T(0)}, v;
+        Loader<T, DIM, L>::data(data, j, x, v);
+        T r2 = sqdist<T, DIM>(c, stage<T, DIM>(x, v, s));
+        if (excl && j == q) r2 = infT<T>();
+        mn = r2 < mn ? r2 : mn;
+      }
+#pragma unroll
+      for (int x = 1; x < 64; x <<= 1) {
+        const T o = __shfl_xor(mn, x);
+        mn = o < mn ? o : mn;
+      }
+      if (lane == 0) mins[wave] = mn;
+      __syncthreads();
+      for (int w = 0; w < kWaves; ++w) mn = mins[w] < mn ? mins[w] : mn;
+      __syncthreads();
+      rk = settle_route<T>(rk, min_bits(mn), hdr);
+    }
+    if (rk == F_FP64) {
+      const FixSums s = fix_query<T, DIM, L, PM>(data, query, q, 0, n, excl, nhp, red);
+      if (threadIdx.x == 0) fix_write<T>(s, q, out_z, out_den);
+      ++fixed;
+    }
+  }
+  // one atomic per workgroup (they take 11 ns each on one address)
+  if (threadIdx.x == 0 && fixed > 0) atomicAdd(count, fixed);
 }
 
 // Merges the chunk partials of split fix-up queries (chunk order, TwoSum) and finalises.
@@ -650,16 +774,55 @@ __global__ __launch_bounds__(kWG) void k_fwd_fixmerge(const int* __restrict__ li
   }
 }
 
-// Bounding box, largest |value| and header in one workgroup, for n <= kSmallBoxMax.
+// Bounding box and largest |value| as maxima: [0..DIM-1] negated minima, [DIM..2 DIM-1] maxima,
+// [2 DIM] the value.
+template <typename T, int DIM>
+struct Box {
+  static constexpr int N = 2 * DIM + 1;
+  T v[N];
+  __device__ __forceinline__ void clear() {
+#pragma unroll
+    for (int k = 0; k < 2 * DIM; ++k) v[k] = -infT<T>();
+    v[2 * DIM] = T(0);
+  }
+  __device__ __forceinline__ void add(const T (&c)[3], T z) {
+#pragma unroll
+    for (int d = 0; d < DIM; ++d) {
+      v[d] = maxT(v[d], -c[d]);
+      v[DIM + d] = maxT(v[DIM + d], c[d]);
+    }
+    v[2 * DIM] = maxT(v[2 * DIM], z < T(0) ? -z : z);
+  }
+  // Over the NT threads of a workgroup; the result is in the first wave.
+  template <int NT>
+  __device__ __forceinline__ void reduce(T (*red)[N]) {
+    constexpr int W = NT / 64;
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+#pragma unroll
+      for (int x = 1; x < 64; x <<= 1) v[k] = maxT(v[k], __shfl_xor(v[k], x));
+    if (lane == 0)
+#pragma unroll
+      for (int k = 0; k < N; ++k) red[threadIdx.x >> 6][k] = v[k];
+    __syncthreads();
+    if (threadIdx.x < 64)
+#pragma unroll
+      for (int k = 0; k < N; ++k) {
+        v[k] = red[lane % W][k];
+#pragma unroll
+        for (int x = 1; x < W; x <<= 1) v[k] = maxT(v[k], __shfl_xor(v[k], x));
+      }
+  }
+};
+
+// Bounding box and header in one workgroup, for n <= kSmallBoxMax.
 template <typename T, int DIM, int L>
 __global__ __launch_bounds__(kSmallBox) void k_bbox_small(DevPts data, int64_t n, double p, int f32s, int rel,
                                                           double* __restrict__ hdr) {
-  constexpr int NV = 2 * DIM + 1;  // minima (negated), maxima, largest |value|: all by max
-  __shared__ T red[kSmallBox / 64][NV];
-  T v[NV];
-#pragma unroll
-  for (int d = 0; d < 2 * DIM; ++d) v[d] = -infT<T>();
-  v[2 * DIM] = T(0);
+  __shared__ T red[kSmallBox / 64][Box<T, DIM>::N];
+  Box<T, DIM> b;
+  b.clear();
   constexpr int kPer = static_cast<int>(kSmallBoxMax / kSmallBox);
 #pragma unroll
   for (int u = 0; u < kPer; ++u) {
@@ -667,34 +830,18 @@ __global__ __launch_bounds__(kSmallBox) void k_bbox_small(DevPts data, int64_t n
     if (j < n) {
       T c[3] = {T(0), T(0), T(0)}, z;
       Loader<T, DIM, L>::data(data, j, c, z);
-#pragma unroll
-      for (int d = 0; d < DIM; ++d) {
-        v[d] = maxT(v[d], -c[d]);
-        v[DIM + d] = maxT(v[DIM + d], c[d]);
-      }
-      v[2 * DIM] = maxT(v[2 * DIM], z < T(0) ? -z : z);
+      b.add(c, z);
     }
   }
-#pragma unroll
-  for (int k = 0; k < NV; ++k)
-#pragma unroll
-    for (int x = 1; x < 64; x <<= 1) v[k] = maxT(v[k], __shfl_xor(v[k], x));
-  const int wave = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0)
-#pragma unroll
-    for (int k = 0; k < NV; ++k) red[wave][k] = v[k];
-  __syncthreads();
+  b.template reduce<kSmallBox>(red);
   if (threadIdx.x == 0) {
-    for (int w = 1; w < kSmallBox / 64; ++w)
-#pragma unroll
-      for (int k = 0; k < NV; ++k) v[k] = maxT(v[k], red[w][k]);
     double mn[3] = {0.0, 0.0, 0.0}, mx[3] = {0.0, 0.0, 0.0};
 #pragma unroll
     for (int d = 0; d < DIM; ++d) {
-      mn[d] = -static_cast<double>(v[d]);
-      mx[d] = static_cast<double>(v[DIM + d]);
+      mn[d] = -static_cast<double>(b.v[d]);
+      mx[d] = static_cast<double>(b.v[DIM + d]);
     }
-    finish_header(hdr, mn, mx, DIM, static_cast<double>(v[2 * DIM]), p, f32s != 0, rel != 0);
+    finish_header(hdr, mn, mx, DIM, static_cast<double>(b.v[2 * DIM]), p, f32s != 0, rel != 0);
   }
 }
 
@@ -702,41 +849,24 @@ __global__ __launch_bounds__(kSmallBox) void k_bbox_small(DevPts data, int64_t n
 // kBboxStride-double record of each workgroup.
 template <typename T, int DIM, int L>
 __global__ __launch_bounds__(kWG) void k_bbox(DevPts data, int64_t n, double* __restrict__ part) {
-  __shared__ double red[kWG];
-  double mn[3] = {__builtin_huge_val(), __builtin_huge_val(), __builtin_huge_val()};
-  double mx[3] = {-__builtin_huge_val(), -__builtin_huge_val(), -__builtin_huge_val()};
-  double vm = 0.0;
+  __shared__ T red[kWG / 64][Box<T, DIM>::N];
+  Box<T, DIM> b;
+  b.clear();
   for (int64_t j = static_cast<int64_t>(blockIdx.x) * kWG + threadIdx.x; j < n;
        j += static_cast<int64_t>(gridDim.x) * kWG) {
-    T c[3] = {T(0), T(0), T(0)}, v;
-    Loader<T, DIM, L>::data(data, j, c, v);
+    T c[3] = {T(0), T(0), T(0)}, z;
+    Loader<T, DIM, L>::data(data, j, c, z);
+    b.add(c, z);
+  }
+  b.template reduce<kWG>(red);
+  if (threadIdx.x == 0) {
+    double* o = part + blockIdx.x * kBboxStride;
 #pragma unroll
     for (int d = 0; d < DIM; ++d) {
-      mn[d] = fmin(mn[d], static_cast<double>(c[d]));
-      mx[d] = fmax(mx[d], static_cast<double>(c[d]));
+      o[d] = -static_cast<double>(b.v[d]);
+      o[3 + d] = static_cast<double>(b.v[DIM + d]);
     }
-    vm = fmax(vm, fabs(static_cast<double>(v)));
-  }
-  const int t = threadIdx.x;
-  red[t] = vm;
-  __syncthreads();
-  for (int s = kWG / 2; s > 0; s >>= 1) {
-    if (t < s) red[t] = fmax(red[t], red[t + s]);
-    __syncthreads();
-  }
-  if (t == 0) part[blockIdx.x * kBboxStride + 6] = red[0];
-  __syncthreads();
-  for (int d = 0; d < DIM; ++d) {
-    for (int pass = 0; pass < 2; ++pass) {
-      red[t] = pass ? mx[d] : mn[d];
-      __syncthreads();
-      for (int s = kWG / 2; s > 0; s >>= 1) {
-        if (t < s) red[t] = pass ? fmax(red[t], red[t + s]) : fmin(red[t], red[t + s]);
-        __syncthreads();
-      }
-      if (t == 0) part[blockIdx.x * kBboxStride + pass * 3 + d] = red[0];
-      __syncthreads();
-    }
+    o[6] = static_cast<double>(b.v[2 * DIM]);
   }
 }
 
@@ -826,11 +956,18 @@ hipError_t launch_fwd_sweep(const FwdArgs& a, bool f64, hipStream_t st) {
 
 template <typename T, int DIM, int L, int PM>
 hipError_t launch_fwd_fixup_t(const FwdArgs& a, hipStream_t st) {
+  if (a.small) {
+    hipLaunchKernelGGL((k_fwd_finish_small<T, DIM, L, PM>), dim3(static_cast<unsigned>((a.m + kWaves - 1) / kWaves)),
+                       dim3(kWG), 0, st, a.data, a.n, a.query, a.m, a.split, -0.5 * a.p, a.flags, a.hdr, a.part,
+                       static_cast<T*>(a.out_z), a.out_den, a.flag, const_cast<int*>(a.count));
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL((k_fwd_fixup<T, DIM, L, PM>), dim3(kFixGrid), dim3(kWG), 0, st, a.data,
                      a.n, a.query, -0.5 * a.p, a.flags, a.list, a.count, a.fix_cmax, a.fpart,
                      static_cast<T*>(a.out_z), a.out_den);
-  hipLaunchKernelGGL((k_fwd_fixmerge<T>), dim3(4), dim3(kWG), 0, st, a.list, a.count, a.fix_cmax,
-                     a.fpart, static_cast<T*>(a.out_z), a.out_den);
+  if (a.fix_cmax > 1)  // data ranges that may be cut into chunks
+    hipLaunchKernelGGL((k_fwd_fixmerge<T>), dim3(4), dim3(kWG), 0, st, a.list, a.count, a.fix_cmax,
+                       a.fpart, static_cast<T*>(a.out_z), a.out_den);
   return hipGetLastError();
 }
 
