@@ -1,5 +1,5 @@
 """Small calls at the limits of their kernels, against the FP64 oracle.  A forward of few pairs
-(both sets up to 16,384, up to 2^25 pairs) is ended by one kernel that merges, checks the nearest
+(both sets up to 16,384, up to 2^26 pairs) is ended by one kernel that merges, checks the nearest
 distances and recomputes the queries sent to FP64; beyond either limit the general kernels do it.
 A third of the queries sit on or next to a data point, so every stage has work, at exponents
 below and above the one under which the FP32 sweep asks for a distance check.  The adjoint's
@@ -30,7 +30,7 @@ def near_case(n, m, dim, prec):
 @pytest.mark.parametrize("prec", ["f32", "f64"])
 @pytest.mark.parametrize("dim,p", [(2, 0.4), (2, 2.0), (3, 3.1)])
 @pytest.mark.parametrize("n,m", [(1, 5), (63, 4), (4099, 7), (16384, 67), (16385, 67), (67, 16384), (67, 16385),
-                                 (16384, 2048), (16384, 2049)])
+                                 (16384, 2048), (16384, 4096), (16384, 4097)])
 def test_forward_limits(prec, dim, p, n, m):
     x, z, q = near_case(n, m, dim, prec)
     d, qq = points(x, z, q, "aoas", prec)
