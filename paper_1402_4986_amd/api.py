@@ -80,7 +80,10 @@ def _cfg(queries_per_lane: int = 0, split: int = 0, near_search: int = 0,
 
 
 def _stream_handle(device) -> int:
-    return torch.cuda.current_stream(device).cuda_stream
+    # The raw handle: building a Stream object for it costs 2 us of a call's 20.
+    if device.index is None:
+        return torch.cuda.current_stream(device).cuda_stream
+    return torch._C._cuda_getCurrentRawStream(device.index)
 
 
 _ws_cache: dict = {}
@@ -92,18 +95,24 @@ def workspace(data: Points, query: Points, precision: str, cfg: Optional[IdwConf
     these point sets, with room for the data-coordinate gradient when need_dx.  Cached per
     (device, current stream) and grown on demand: calls enqueued on one stream run in order,
     so they may share it, while work on another stream gets its own."""
-    lib = _lib.load()
+    return _workspace(_lib.load(), data.c(), query.c(), data.device, _stream_handle(data.device), precision, cfg,
+                      backward, need_dx)
+
+
+def _workspace(lib, dc: IdwPoints, qc: IdwPoints, device, stream: int, precision: str, cfg: Optional[IdwConfig],
+               backward: bool, need_dx: bool) -> torch.Tensor:
+    """workspace() for descriptors and a stream that the caller has already made for its own call
+    (made twice, they are 5 us of a small forward's 20 on the host)."""
     need = ctypes.c_size_t()
-    dc, qc = data.c(), query.c()
     flags = (_lib.NEED_DZ | _lib.NEED_DP | _lib.NEED_DQ) if backward else 0
     if backward and need_dx:
         flags |= _lib.NEED_DX
     check(lib.idw_workspace_size(ctypes.byref(dc), ctypes.byref(qc), _lib.PRECISION_CODES[precision], flags,
                                  ctypes.byref(cfg) if cfg is not None else None, ctypes.byref(need)))
-    key = (str(data.device), _stream_handle(data.device))
+    key = (device, stream)
     ws = _ws_cache.get(key)
     if ws is None or ws.numel() < need.value:
-        ws = torch.empty(max(need.value, 256), dtype=torch.uint8, device=data.device)
+        ws = torch.empty(max(need.value, 256), dtype=torch.uint8, device=device)
         _ws_cache[key] = ws
     return ws
 
@@ -122,12 +131,12 @@ def forward(data: Points, query: Points, p: float, precision: str = "f32", exclu
     if out_den is None:
         out_den = torch.empty(m, dtype=torch.float64, device=dev)
     cfg = _cfg(queries_per_lane, split, near_search)
+    dc, qc, stream = data.c(), query.c(), _stream_handle(dev)
     if ws is None:
-        ws = workspace(data, query, precision, cfg, backward=False)
-    dc, qc = data.c(), query.c()
+        ws = _workspace(lib, dc, qc, dev, stream, precision, cfg, False, False)
     check(lib.idw_forward(ctypes.byref(dc), ctypes.byref(qc), float(p), _lib.PRECISION_CODES[precision],
                           _lib.EXCLUDE_SELF if exclude_self else 0, _ptr(out_z), _ptr(out_den), _ptr(ws),
-                          ws.numel(), _stream_handle(dev), ctypes.byref(cfg) if cfg is not None else None))
+                          ws.numel(), stream, ctypes.byref(cfg) if cfg is not None else None))
     return out_z, out_den
 
 
@@ -152,12 +161,12 @@ def backward(data: Points, query: Points, p: float, grad_out: torch.Tensor, save
     flags = (_lib.EXCLUDE_SELF if exclude_self else 0) | (_lib.NEED_DZ if need_dz else 0) \
         | (_lib.NEED_DP if need_dp else 0) | (_lib.NEED_DQ if need_dq else 0) | (_lib.NEED_DX if need_dx else 0)
     cfg = _cfg(near_search=near_search, separate=separate)
+    dc, qc, stream = data.c(), query.c(), _stream_handle(dev)
     if ws is None:
-        ws = workspace(data, query, precision, cfg, need_dx=need_dx)
-    dc, qc = data.c(), query.c()
+        ws = _workspace(lib, dc, qc, dev, stream, precision, cfg, True, need_dx)
     check(lib.idw_backward(ctypes.byref(dc), ctypes.byref(qc), float(p), _lib.PRECISION_CODES[precision], flags,
                            _ptr(grad_out.contiguous()), _ptr(saved_z), _ptr(saved_den), _ptr(dz), _ptr(dp),
-                           _ptr(dq), _ptr(dx), _ptr(ws), ws.numel(), _stream_handle(dev),
+                           _ptr(dq), _ptr(dx), _ptr(ws), ws.numel(), stream,
                            ctypes.byref(cfg) if cfg is not None else None))
     if need_dx:
         return dz, dp, dq, dx
