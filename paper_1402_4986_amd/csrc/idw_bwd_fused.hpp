@@ -311,10 +311,13 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE, 8))) vo
 
 // Queries per wave: as many as the registers of 4 waves per SIMD hold.  16 in 2-D (48 sums) and
 // in 3-D (64 sums; 131,072 x 1M points, p = 2: 47.0 ms against 49.0 with 8); 8 where the scales
-// of the relative weights or the 3-D X sums would make 16 spill.
+// of the relative weights would make 16 spill.  With the 3-D X sums 16 fit once the FP64 sums
+// over lanes are left in memory (GSUM), and the staging, folding and row traffic of a tile are
+// shared by twice the queries (131,072 x 262,144, p = 2 with dx: 83 cycles per pair and wave with
+// 8 queries, 80 with 12, 74 with 16).
 template <int DIM, bool NDX, bool REL>
 struct FusedRows {
-  static constexpr int R = REL || (DIM == 3 && NDX) ? 8 : 16;
+  static constexpr int R = REL ? 8 : 16;
 };
 constexpr int kFusedWaves = 8;
 constexpr int kFlush = 4096;  // data points between the sums over lanes (64 per lane)
@@ -347,8 +350,10 @@ __global__ __launch_bounds__(64 * kFusedWaves) __attribute__((amdgpu_waves_per_e
   __shared__ RecTile<float, 3, TILE> tile[2];
   __shared__ float zred[kFusedWaves][TILE];     // per-wave dz sums of the tile; rows of the addition over lanes
   __shared__ float xred[NDX ? kFusedWaves : 1][NDX ? DIM * TILE : 1];  // per-wave X sums
-  // the FP64 sums over lanes, in registers where LDS is taken by the X sums
+  // The FP64 sums over lanes: in LDS, or, where the X sums take it, in registers, or, where 16
+  // queries with X sums leave none (3-D), in the query's partial itself.
   constexpr bool LSUM = !NDX && NR > 0;
+  constexpr bool GSUM = NDX && DIM == 3 && !REL;
   __shared__ double lsum[LSUM ? kFusedWaves : 1][LSUM ? NR : 1][LSUM ? 64 : 1];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -422,7 +427,6 @@ __global__ __launch_bounds__(64 * kFusedWaves) __attribute__((amdgpu_waves_per_e
     }
     constexpr int NA = NC > 0 ? NC : 1;
     float acc[NA][R];           // P, then G per coordinate
-    double sums[LSUM || NR == 0 ? 1 : NR];
     float own[NA];              // EXCL, lane r: query r's sums over its leave-one-out block
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
@@ -430,12 +434,15 @@ __global__ __launch_bounds__(64 * kFusedWaves) __attribute__((amdgpu_waves_per_e
 #pragma unroll
       for (int r = 0; r < R; ++r) acc[c][r] = 0.f;
     }
+    double sums[LSUM || GSUM || NR == 0 ? 1 : NR];
+    if constexpr (!GSUM) {
 #pragma unroll
-    for (int k = 0; k < NR; ++k) {
-      if constexpr (LSUM)
-        lsum[wave][k][lane] = 0.0;
-      else
-        sums[k] = 0.0;
+      for (int k = 0; k < NR; ++k) {
+        if constexpr (LSUM)
+          lsum[wave][k][lane] = 0.0;
+        else
+          sums[k] = 0.0;
+      }
     }
 
     // The lane's point against the wave's queries.  Every layer of GQ independent operations
@@ -538,7 +545,9 @@ __global__ __launch_bounds__(64 * kFusedWaves) __attribute__((amdgpu_waves_per_e
 
     // Adds the per-lane sums over the lanes: 8 of them at a time go through this wave's row of
     // zred as 8 rows of 64, of which lane l adds 8 values of row l / 8 into its FP64 sum.
-    auto flush = [&]() {
+    // With GSUM, lanes 8 i .. 8 i + 7 add theirs together and lane 8 i adds that to its query's
+    // partial (component c of query 8 h + i in round k = (c R) / 8 + h).
+    auto flush = [&](bool start, bool last) {
       float* row = zred[wave];
 #pragma unroll
       for (int k = 0; k < NR; ++k) {
@@ -557,8 +566,21 @@ __global__ __launch_bounds__(64 * kFusedWaves) __attribute__((amdgpu_waves_per_e
         const double v = static_cast<double>(((a.x + a.y) + (a.z + a.w)) + ((b.x + b.y) + (b.z + b.w)));
         if constexpr (LSUM)
           lsum[wave][k][lane] += v;  // this lane's own element
-        else
+        else if constexpr (!GSUM)
           sums[k] += v;
+        else {
+          const int c = 8 * k / R, r = 8 * k % R + lane / 8;
+          double t = v;
+#pragma unroll
+          for (int x = 1; x < 8; x <<= 1) t += shfl_xor64(t, x);
+          if constexpr (EXCL) {
+            if (last) t += static_cast<double>(__shfl(own[c], r));
+          }
+          if ((lane & 7) == 0 && qw + r < m) {
+            double* o = &part_q[static_cast<int64_t>(blockIdx.y) * m + qw + r].x + (NDP ? c : c + 1);
+            *o = start ? t : *o + t;
+          }
+        }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
       }
@@ -614,6 +636,13 @@ __global__ __launch_bounds__(64 * kFusedWaves) __attribute__((amdgpu_waves_per_e
           }
         }
       }
+      double xold[3] = {0.0, 0.0, 0.0};  // loaded here, where the batches' registers are free
+      if constexpr (GSUM) {
+        if (!first && j < je) {
+#pragma unroll
+          for (int e = 0; e < DIM; ++e) xold[e] = xrow[j * DIM + e];
+        }
+      }
       __syncthreads();  // zred complete; tile t fully consumed
       // dz: add the waves' sums in a fixed order and fold into this group's row.  The stores
       // come after the next tile has been put: a wait for its loads, which were issued before
@@ -626,7 +655,7 @@ __global__ __launch_bounds__(64 * kFusedWaves) __attribute__((amdgpu_waves_per_e
       double xv[3];
       if constexpr (NDX) {
 #pragma unroll
-        for (int e = 0; e < DIM; ++e) xv[e] = waves(&xred[0][e * TILE + tid], DIM * TILE);
+        for (int e = 0; e < DIM; ++e) xv[e] = xold[e] + waves(&xred[0][e * TILE + tid], DIM * TILE);
       }
       if (t + 1 < ntiles) put((t + 1) & 1);
       __syncthreads();
@@ -634,14 +663,15 @@ __global__ __launch_bounds__(64 * kFusedWaves) __attribute__((amdgpu_waves_per_e
         zrow[j] = zold;
         if constexpr (NDX) {
 #pragma unroll
-          for (int e = 0; e < DIM; ++e) xrow[j * DIM + e] = first ? xv[e] : xrow[j * DIM + e] + xv[e];
+          for (int e = 0; e < DIM; ++e) xrow[j * DIM + e] = GSUM || first ? xv[e] : xrow[j * DIM + e] + xv[e];
         }
       }
       if constexpr (NC > 0) {
-        if ((t + 1) % (kFlush / TILE) == 0 || t + 1 == ntiles) flush();  // own row of zred only
+        if ((t + 1) % (kFlush / TILE) == 0 || t + 1 == ntiles)
+          flush(t < kFlush / TILE, t + 1 == ntiles);  // own row of zred only
       }
     }
-    if constexpr (NC > 0) {
+    if constexpr (NC > 0 && !GSUM) {
       // lanes 8 i .. 8 i + 7 hold sum 8 k + i: query r = 8 h + i of component c at k = (c R + 8 h) / 8
 #pragma unroll
       for (int h = 0; h < R / 8; ++h) {
