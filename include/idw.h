@@ -165,8 +165,8 @@ int idw_record_bytes(int32_t layout, int32_t dim, int32_t precision, int32_t is_
  * idw_backward with those gradients (one workspace then serves both; the forward uses a
  * prefix of it, and a backward without IDW_NEED_DX a prefix of the one with it).  The
  * forward keeps the partial sums of its data chunks (268 MB at n = m = 2^20); the fused
- * adjoint per-range query partials and per-group data partials (3.2 GB there, plus dim x 1.1
- * GB, in FP64 dim x 2.1 GB, for IDW_NEED_DX); each such array stays within 2 GiB (dim times that for
+ * adjoint per-range query partials and per-group data partials (2.5 GB there, in FP64 3.3 GB,
+ * plus dim x 2.1 GB for IDW_NEED_DX); each such array stays within 2 GiB (dim times that for
  * the dx partials) or one row of the point set, whatever the sizes.  For 65,536 <= n <=
  * 2^26 (and near_search = 0) the forward part holds the grid of the nearest-distance
  * searches: about 18 B per data point (34 B in FP64) and 4 B per query.  Host only. */

@@ -626,7 +626,7 @@ __device__ __forceinline__ uint8_t route_of(double den, const double* __restrict
 constexpr int kBboxStride = 8;
 
 // Data points up to which one workgroup of kSmallBox threads takes the bounding box and fills
-// the header (16 points per thread): 4.6 us at 1,024 points in FP32, 8.8 us at 10,240 in FP64,
+// the header (16 points per thread): 4.9 us at 1,024 points in FP32, 7.8 us at 10,240 in FP64,
 // where the partial boxes and their reduction took two launches of 11.7 us together.
 constexpr int kSmallBox = 1024;
 constexpr int64_t kSmallBoxMax = 16384;

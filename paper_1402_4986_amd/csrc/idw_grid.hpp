@@ -145,7 +145,7 @@ __device__ __forceinline__ T grid_r2(const T (&q)[3], const P4<T>& r) {
 }
 
 // ---- fixed-radius check of the candidate queries (list, hint[GI_GRID] of them) ----
-// Writes F_FP64 / F_FP32 as k_near_finish would, or appends the query to blist.
+// Writes F_FP64 / F_FP32 as the settling of the routes would, or appends the query to blist.
 template <typename T, int DIM, int L, bool EXCL>
 __global__ __launch_bounds__(kWG) void k_grid_check(DevPts query, const int* __restrict__ list,
                                                     const double* __restrict__ hdr, int* __restrict__ hint,
