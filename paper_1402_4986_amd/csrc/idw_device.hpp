@@ -288,6 +288,7 @@ __device__ __forceinline__ double log2_t(double a) {
 }
 
 __device__ __forceinline__ double exp2_t(double x) {
+  x = fmax(x, -1100.0);  // 0 for -inf (a data point at infinity) and NaN
   constexpr double C1 = 0.69314718055994530942;  // ln 2
   constexpr double C2 = C1 * C1 / 2.0, C3 = C2 * C1 / 3.0, C4 = C3 * C1 / 4.0, C5 = C4 * C1 / 5.0;
   constexpr double kMagic = 0x1.8p52;
@@ -357,13 +358,13 @@ __device__ __forceinline__ void pow_table_init(double nh) {
 
 constexpr double kPowLow = 3.0;
 
-// a >= 0; DEG: the last power of the binomial series (6 for |nh| <= kPowLow, else 10).
+// a >= 0 (NaN gives 0: the forward looks for it in the records); DEG: the last power of the binomial series (6 for |nh| <= kPowLow, else 10).
 template <int DEG = 10>
 __device__ __forceinline__ double pow_t(double a) {
   const unsigned long long b = __builtin_bit_cast(unsigned long long, a);
   const unsigned int hi = static_cast<unsigned int>(b >> 32);
   const int k = static_cast<int>((hi >> 12) & (kLogTab - 1));
-  const int ei = static_cast<int>(hi >> 20);
+  const int ei = static_cast<int>((hi >> 20) & 0x7ff);
   const double m = __builtin_bit_cast(double, (b & 0x000fffffffffffffull) | 0x3ff0000000000000ull);
   const double2 t = pow_mtable()[k];
   const double r = fma(m, t.x, -1.0);

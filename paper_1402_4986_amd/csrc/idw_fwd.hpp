@@ -339,6 +339,10 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(Tune::WMIN,
     dacc[k].zero();
   }
 
+  // The tables' weight of a NaN distance is 0: a NaN coordinate is found here, once per record
+  // (a comparison per pair cost 6 of 137 cycles).
+  constexpr bool kSeekNan = sizeof(T) == 8 && PM == PM_GEN;
+  bool bad = false;
   T rc[2][3], rv[2];
   auto fetch = [&](int t) {
 #pragma unroll
@@ -346,6 +350,10 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(Tune::WMIN,
       const int64_t j = jb + static_cast<int64_t>(t) * kTile + u * kWG + tid;
       if (j < je) {
         Loader<T, DIM, L>::data(data, j, rc[u], rv[u]);
+        if constexpr (kSeekNan) {
+#pragma unroll
+          for (int d = 0; d < DIM; ++d) bad |= rc[u][d] != rc[u][d];
+        }
       } else {  // padding record: far away, zero value -> weight (near) 0
         rc[u][0] = rc[u][1] = rc[u][2] = padT<T>();
         rv[u] = T(0);
@@ -391,11 +399,13 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(Tune::WMIN,
     __syncthreads();
   }
 
+  if constexpr (kSeekNan) bad = __syncthreads_or(bad);
 #pragma unroll
   for (int k = 0; k < Q; ++k) {
     if (qi[k] < m) {
       double num = nacc[k].value();
       double den = dacc[k].value();
+      if (kSeekNan && bad) den = __builtin_nan("");  // to the FP64 fix-up
       if constexpr (REL) {
         num *= fs[k];
         den *= fs[k];
