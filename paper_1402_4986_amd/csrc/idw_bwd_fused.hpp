@@ -492,7 +492,8 @@ __global__ __launch_bounds__(64 * kFusedWaves) __attribute__((amdgpu_waves_per_e
     };
 
     // Leave-one-out: the lanes whose points are the wave's own queries against those queries,
-    // one query at a time, the self pair left out.
+    // one query at a time, the self pair left out (at most R - 1 terms, added over the lanes in
+    // FP32 and then with the other sums in FP64).
     auto near_self = [&](const P4<float>& d, int self, float& zs, float (&xs)[3]) {
       float vq[3], vz, va, vs, vk, vx;
       prepare(vq, vz, va, vs, vk, vx);
@@ -544,7 +545,9 @@ __global__ __launch_bounds__(64 * kFusedWaves) __attribute__((amdgpu_waves_per_e
     };
 
     // Adds the per-lane sums over the lanes: 8 of them at a time go through this wave's row of
-    // zred as 8 rows of 64, of which lane l adds 8 values of row l / 8 into its FP64 sum.
+    // zred as 8 rows of 64, of which lane l adds 8 values of row l / 8 into its FP64 sum.  They
+    // are widened before they are added, so that at most 64 FP32 terms lie between two FP64
+    // additions (0.2-0.8% of the sweep: 131,072 x 131,072, p = 2, 4.94 -> 4.95 ms).
     // With GSUM, lanes 8 i .. 8 i + 7 add theirs together and lane 8 i adds that to its query's
     // partial (component c of query 8 h + i in round k = (c R) / 8 + h).
     auto flush = [&](bool start, bool last) {
@@ -563,7 +566,8 @@ __global__ __launch_bounds__(64 * kFusedWaves) __attribute__((amdgpu_waves_per_e
         __builtin_amdgcn_wave_barrier();
         const P4<float> a = *reinterpret_cast<const P4<float>*>(&row[lane * 8]);
         const P4<float> b = *reinterpret_cast<const P4<float>*>(&row[lane * 8 + 4]);
-        const double v = static_cast<double>(((a.x + a.y) + (a.z + a.w)) + ((b.x + b.y) + (b.z + b.w)));
+        const double v = ((static_cast<double>(a.x) + a.y) + (static_cast<double>(a.z) + a.w)) +
+                         ((static_cast<double>(b.x) + b.y) + (static_cast<double>(b.z) + b.w));
         if constexpr (LSUM)
           lsum[wave][k][lane] += v;  // this lane's own element
         else if constexpr (!GSUM)
@@ -644,7 +648,9 @@ __global__ __launch_bounds__(64 * kFusedWaves) __attribute__((amdgpu_waves_per_e
         }
       }
       __syncthreads();  // zred complete; tile t fully consumed
-      // dz: add the waves' sums in a fixed order and fold into this group's row.  The stores
+      // dz: add the waves' sums in a fixed order and fold into this group's row.  FP32: 16 terms
+      // a wave and three additions over the waves, 19 roundings at most (in FP64 the additions
+      // cost 0.5% with dz alone, but 12% with the 3-D X sums, whose registers then spill).  The stores
       // come after the next tile has been put: a wait for its loads, which were issued before
       // them, would otherwise wait for the stores too.
       auto waves = [&](const float* v, int stride) {
