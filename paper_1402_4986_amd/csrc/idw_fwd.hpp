@@ -213,9 +213,9 @@ __device__ __forceinline__ void fwd_tile_run(const RecTile<float, DIM, kTile>& t
 
 // Whole 64-record blocks [0, end) in FP64 for the reciprocal weights (p = 2 and 4), without a
 // self pair: four records' reciprocals from one (rcp64_w4).  Bound by FP64 issue: 8 instructions
-// and a quarter of an estimate, about 43 cycles per pair and wave against 51.5.  The next
-// group's records are read ahead.  65,536 x 262,144, per pair and wave: p = 2 53.9 -> 47.8
-// cycles, p = 4 58.7 -> 52.5; 3-D 63.7 -> 57.5 and 68.4 -> 63.
+// and a quarter of an estimate, about 44 cycles per pair and wave against 51.5 with a reciprocal
+// each.  The next group's records are read ahead.  Calls of 131,072 x 131,072: p = 2 5.75 -> 5.16
+// ms, p = 4 6.22 -> 5.62; 3-D 6.72 -> 6.30 and 7.24 -> 6.84.
 template <int DIM, int PM, int Q, typename Acc>
 __device__ __forceinline__ void fwd_tile_rcp4(const RecTile<double, DIM, kTile>& tl, int end,
                                               const double (&qc)[Q][3], Acc (&num)[Q], Acc (&den)[Q]) {
