@@ -574,30 +574,28 @@ __device__ __forceinline__ int fix_chunks(int cnt, int cmax) {
 
 constexpr int kWaves = kWG / 64;
 
-// Sums over data points [j0, j1) of query i in FP64, over the workgroup; every thread gets the
-// totals.  Call uniformly.
+// A lane's FP64 sums for one query, and its totals.
 struct FixSums {
   double num, den, hz;
   long long h;
 };
-template <typename T, int DIM, int L, int PM>
-__device__ __forceinline__ FixSums fix_query(const DevPts& data, const DevPts& query, int64_t i, int64_t j0, int64_t j1,
-                                             bool excl, double nhp, FixSums (&red)[kWaves]) {
-  T qt[3] = {T(0), T(0), T(0)};
-  Loader<T, DIM, L>::query(query, i, qt);
+struct FixAcc {
   NSum num, den;
   double hz = 0.0;
   long long h = 0;
-  for (int64_t j = j0 + threadIdx.x; j < j1; j += kWG) {
-    if (excl && j == i) continue;
-    T cc[3] = {T(0), T(0), T(0)}, v;
-    Loader<T, DIM, L>::data(data, j, cc, v);
+  template <typename T, int DIM>
+  static __device__ __forceinline__ double dist(const T (&qt)[3], const T (&cc)[3]) {
     double r2 = 0.0;
 #pragma unroll
     for (int d = 0; d < DIM; ++d) {
       const double e = static_cast<double>(qt[d]) - static_cast<double>(cc[d]);
       r2 += e * e;
     }
+    return r2;
+  }
+  template <typename T, int DIM, int PM>
+  __device__ __forceinline__ void add(const T (&qt)[3], const T (&cc)[3], T v, double nhp) {
+    const double r2 = dist<T, DIM>(qt, cc);
     if (r2 == 0.0) {
       ++h;
       hz += static_cast<double>(v);
@@ -607,20 +605,22 @@ __device__ __forceinline__ FixSums fix_query(const DevPts& data, const DevPts& q
       den.add(wgt);
     }
   }
-  // a tree over the lanes of each wave, then the waves in order: two barriers, where four
-  // block_sum()s have 40
-  FixSums s = {num.value(), den.value(), hz, h};
+  // A tree over the lanes of each wave; the first lane leaves the wave's sums in *out.
+  __device__ __forceinline__ void reduce(FixSums* out) const {
+    FixSums s = {num.value(), den.value(), hz, h};
 #pragma unroll
-  for (int x = 1; x < 64; x <<= 1) {
-    s.num += __shfl_xor(s.num, x);
-    s.den += __shfl_xor(s.den, x);
-    s.hz += __shfl_xor(s.hz, x);
-    s.h += __shfl_xor(s.h, x);
+    for (int x = 1; x < 64; x <<= 1) {
+      s.num += __shfl_xor(s.num, x);
+      s.den += __shfl_xor(s.den, x);
+      s.hz += __shfl_xor(s.hz, x);
+      s.h += __shfl_xor(s.h, x);
+    }
+    if ((threadIdx.x & 63) == 0) *out = s;
   }
-  __syncthreads();  // the last call's totals are read
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
-  __syncthreads();
-  s = red[0];
+};
+// The waves' sums in order.
+__device__ __forceinline__ FixSums fix_total(const FixSums (&red)[kWaves]) {
+  FixSums s = red[0];
 #pragma unroll
   for (int w = 1; w < kWaves; ++w) {
     s.num += red[w].num;
@@ -629,6 +629,106 @@ __device__ __forceinline__ FixSums fix_query(const DevPts& data, const DevPts& q
     s.h += red[w].h;
   }
   return s;
+}
+
+// Sums over data points [j0, j1) of query i in FP64, over the workgroup; every thread gets the
+// totals (two barriers, where four block_sum()s have 40).  Call uniformly.
+template <typename T, int DIM, int L, int PM>
+__device__ __forceinline__ FixSums fix_query(const DevPts& data, const DevPts& query, int64_t i, int64_t j0, int64_t j1,
+                                             bool excl, double nhp, FixSums (&red)[kWaves]) {
+  T qt[3] = {T(0), T(0), T(0)};
+  Loader<T, DIM, L>::query(query, i, qt);
+  FixAcc acc;
+  for (int64_t j = j0 + threadIdx.x; j < j1; j += kWG) {
+    if (excl && j == i) continue;
+    T cc[3] = {T(0), T(0), T(0)}, v;
+    Loader<T, DIM, L>::data(data, j, cc, v);
+    acc.template add<T, DIM, PM>(qt, cc, v, nhp);
+  }
+  __syncthreads();  // the last call's totals are read
+  acc.reduce(&red[threadIdx.x >> 6]);
+  __syncthreads();
+  return fix_total(red);
+}
+
+// The same sums for the queries i[0] and i[1], each record read once.  At general p, whose weight is
+// a long chain of operations, hits go through as selects so that the two chains overlap (four
+// hits, 16,384 x 1,000, p = 1.7: 87 us against 97); the other weights keep the branch (all hits,
+// 8,192 x 8,192, p = 2: 126 us against 139).  red: a row per query.
+template <typename T, int DIM, int L, int PM>
+__device__ __forceinline__ void fix_pair(const DevPts& data, const DevPts& query, const int64_t (&i)[2], int64_t n,
+                                         bool excl, double nhp, FixSums (&red)[2][kWaves]) {
+  T qt[2][3] = {};
+  FixAcc acc[2];
+#pragma unroll
+  for (int k = 0; k < 2; ++k) Loader<T, DIM, L>::query(query, i[k], qt[k]);
+  for (int64_t j = threadIdx.x; j < n; j += kWG) {
+    T cc[3] = {T(0), T(0), T(0)}, v;
+    Loader<T, DIM, L>::data(data, j, cc, v);
+    if constexpr (PM == PM_GEN) {
+      double w[2];
+      bool hit[2];
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const double r2 = FixAcc::dist<T, DIM>(qt[k], cc);
+        hit[k] = r2 == 0.0;
+        w[k] = weight<PM>(r2, nhp);
+      }
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const bool self = excl && j == i[k];
+        const double z = static_cast<double>(v);
+        acc[k].h += hit[k] && !self ? 1 : 0;
+        acc[k].hz += hit[k] && !self ? z : 0.0;
+        acc[k].num.add(hit[k] || self ? 0.0 : w[k] * z);
+        acc[k].den.add(hit[k] || self ? 0.0 : w[k]);
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < 2; ++k)
+        if (!(excl && j == i[k])) acc[k].template add<T, DIM, PM>(qt[k], cc, v, nhp);
+    }
+  }
+  __syncthreads();  // the last call's totals are read
+#pragma unroll
+  for (int k = 0; k < 2; ++k) acc[k].reduce(&red[k][threadIdx.x >> 6]);
+  __syncthreads();
+}
+
+// Smallest squared distances (scaled units) of the queries q[0..K-1] over a workgroup's share of
+// a pass over the data, per wave: mins[k][wave].  Queries past m take any place.
+template <typename T, int DIM, int L, int K>
+__device__ __forceinline__ void near_min(const DevPts& data, const DevPts& query, const int64_t (&q)[K], int64_t m,
+                                         int64_t n, bool excl, T s, T (*mins)[kWaves]) {
+  T mn[K], c[K][3];
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    mn[k] = infT<T>();
+    c[k][0] = c[k][1] = c[k][2] = T(0);
+    if (q[k] < m) Loader<T, DIM, L>::query(query, q[k], c[k]);
+#pragma unroll
+    for (int d = 0; d < 3; ++d) c[k][d] *= s;
+  }
+  for (int64_t j = threadIdx.x; j < n; j += kWG) {
+    T x[3] = {T(0), T(0), T(0)}, v;
+    Loader<T, DIM, L>::data(data, j, x, v);
+    const P4<T> rec = stage<T, DIM>(x, v, s);
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      T r2 = sqdist<T, DIM>(c[k], rec);
+      if (excl && j == q[k]) r2 = infT<T>();
+      mn[k] = r2 < mn[k] ? r2 : mn[k];
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+#pragma unroll
+    for (int x = 1; x < 64; x <<= 1) {
+      const T o = __shfl_xor(mn[k], x);
+      mn[k] = o < mn[k] ? o : mn[k];
+    }
+    if ((threadIdx.x & 63) == 0) mins[k][threadIdx.x >> 6] = mn[k];
+  }
 }
 
 template <typename T>
@@ -669,22 +769,25 @@ __global__ __launch_bounds__(kWG) void k_fwd_fixup(DevPts data, int64_t n, DevPt
 
 // Everything after the sweep of a small forward (small_call) in one launch: a wave merges its
 // query's partials (lane c takes chunks c, c + 64, ..., then a fixed tree over the lanes) and
-// finds the route; the workgroup then settles its candidates by their nearest distance and
-// recomputes the queries routed to FP64, one at a time.  Such a call is mostly launches: with
-// this kernel in place of five (merge, nearest-distance check, settling, fix-up and its merge) a
-// call of 1,024 x 1,000 takes 13.5 us in place of 28.7, one of 4,096 x 4,099 20 in place of 32.
-
+// finds the route; the workgroup then settles its candidates by their nearest distance, in one
+// pass over the data, and recomputes the queries routed to FP64, two in a pass.  Such a call is
+// mostly launches: with this kernel in place of five (merge, nearest-distance check, settling,
+// fix-up and its merge) a call of 1,024 x 1,000 takes 13 us in place of 28.7, one of 4,096 x 4,099
+// 20 in place of 32.  A pass of one workgroup is a chain of loads and FP64 operations, 17 us (p = 2)
+// or 26 (p = 1.7) over 16,384 points: one for each of four neighbouring hits made a call of 16,384
+// x 1,000 slower (84 and 116 us) than the five kernels, which cut a query's data among workgroups
+// (80 and 107); in pairs it takes 66 and 87.
 template <typename T, int DIM, int L, int PM>
-__global__ __launch_bounds__(kWG) void k_fwd_finish_small(DevPts data, int64_t n, DevPts query, int64_t m, int split,
+__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_fwd_finish_small(DevPts data, int64_t n, DevPts query, int64_t m, int split,
                                                           double nhp, unsigned flags,
                                                           const double* __restrict__ hdr,
                                                           const double2* __restrict__ part, T* __restrict__ out_z,
                                                           double* __restrict__ out_den,
                                                           const uint8_t* __restrict__ route,
                                                           int* __restrict__ count) {
-  __shared__ FixSums red[kWaves];
+  __shared__ FixSums red[2][kWaves];
   __shared__ uint8_t routes[kWaves];
-  __shared__ T mins[kWaves];
+  __shared__ T mins[kWaves][kWaves];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const bool excl = (flags & 1u) != 0;
   const int64_t first = static_cast<int64_t>(blockIdx.x) * kWaves;
@@ -718,39 +821,44 @@ __global__ __launch_bounds__(kWG) void k_fwd_finish_small(DevPts data, int64_t n
   }
   if (lane == 0) routes[wave] = r;
   if (!__syncthreads_or(lane == 0 && r != F_FP32)) return;
-  int fixed = 0;
-  for (int k = 0; k < kWaves; ++k) {  // uniform over the workgroup
-    uint8_t rk = routes[k];
-    const int64_t q = first + k;
-    if (rk == F_CANDIDATE) {
-      const T s = static_cast<T>(hdr[H_SCALE]);
-      T c[3] = {T(0), T(0), T(0)};
-      Loader<T, DIM, L>::query(query, q, c);
+  unsigned cand = 0, fp64 = 0;  // bit k: the group's query k; uniform over the workgroup
 #pragma unroll
-      for (int d = 0; d < 3; ++d) c[d] *= s;
-      T mn = infT<T>();
-      for (int64_t j = threadIdx.x; j < n; j += kWG) {
-        T x[3] = {T(0), T(0), T(0)}, v;
-        Loader<T, DIM, L>::data(data, j, x, v);
-        T r2 = sqdist<T, DIM>(c, stage<T, DIM>(x, v, s));
-        if (excl && j == q) r2 = infT<T>();
-        mn = r2 < mn ? r2 : mn;
-      }
-#pragma unroll
-      for (int x = 1; x < 64; x <<= 1) {
-        const T o = __shfl_xor(mn, x);
-        mn = o < mn ? o : mn;
-      }
-      if (lane == 0) mins[wave] = mn;
-      __syncthreads();
-      for (int w = 0; w < kWaves; ++w) mn = mins[w] < mn ? mins[w] : mn;
-      __syncthreads();
-      rk = settle_route<T>(rk, min_bits(mn), hdr);
+  for (int k = 0; k < kWaves; ++k) {
+    cand |= routes[k] == F_CANDIDATE ? 1u << k : 0u;
+    fp64 |= routes[k] == F_FP64 ? 1u << k : 0u;
+  }
+  if (cand) {
+    const T s = static_cast<T>(hdr[H_SCALE]);
+    if (cand & (cand - 1)) {
+      const int64_t q[kWaves] = {first, first + 1, first + 2, first + 3};
+      near_min<T, DIM, L>(data, query, q, m, n, excl, s, mins);
+    } else {
+      const int64_t q[1] = {first + __ffs(cand) - 1};
+      near_min<T, DIM, L>(data, query, q, m, n, excl, s, mins);
     }
-    if (rk == F_FP64) {
-      const FixSums s = fix_query<T, DIM, L, PM>(data, query, q, 0, n, excl, nhp, red);
-      if (threadIdx.x == 0) fix_write<T>(s, q, out_z, out_den);
-      ++fixed;
+    __syncthreads();
+    for (unsigned c = cand; c; c &= c - 1) {
+      const int k = __ffs(c) - 1;
+      const T (&row)[kWaves] = mins[cand & (cand - 1) ? k : 0];
+      T mn = row[0];
+#pragma unroll
+      for (int w = 1; w < kWaves; ++w) mn = row[w] < mn ? row[w] : mn;
+      if (settle_route<T>(F_CANDIDATE, min_bits(mn), hdr) == F_FP64) fp64 |= 1u << k;
+    }
+  }
+  fp64 = __builtin_amdgcn_readfirstlane(fp64);
+  const int fixed = __popc(fp64);
+  while (fp64) {  // two at a time
+    const int k0 = __ffs(fp64) - 1;
+    fp64 &= fp64 - 1;
+    if (fp64) {
+      const int k1 = __ffs(fp64) - 1;
+      fp64 &= fp64 - 1;
+      fix_pair<T, DIM, L, PM>(data, query, {first + k0, first + k1}, n, excl, nhp, red);
+      if (lane == 0 && (wave == k0 || wave == k1)) fix_write<T>(fix_total(red[wave == k1]), i, out_z, out_den);
+    } else {
+      const FixSums s = fix_query<T, DIM, L, PM>(data, query, first + k0, 0, n, excl, nhp, red[0]);
+      if (lane == 0 && wave == k0) fix_write<T>(s, i, out_z, out_den);
     }
   }
   // one atomic per workgroup (they take 11 ns each on one address)

@@ -150,11 +150,12 @@ constexpr int kFixGrid = 1024;    // workgroups of the FP64 fix-up kernels
 constexpr int kCountBlock = 4096; // flags per compaction block (16 per thread)
 
 // Forwards that k_fwd_finish_small ends: few pairs, so that even if every query is a candidate or
-// a hit (one pass over the data each, by one workgroup of four queries) the call is no longer
-// than with the general kernels (16,384 x 4,096: 38.0 us against 41.4, all hits 141 against 152,
-// all candidates 82 against 84; 10,240 x 10,240, twice the pairs: 43.8 against 45.6, but all
-// candidates 104 against 94); and neither set so long that a workgroup per four queries, or one
-// workgroup's pass over the data, would be.
+// a hit (passes over the data by one workgroup of four queries) the call is no longer than with
+// the general kernels (16,384 x 4,096: 40.6 us against 41.4, all hits 133 against 152, all
+// candidates 65 against 84), the line having been set when each query took a pass of its own
+// (10,240 x 10,240, twice the pairs: 43.8 against 45.6, but all candidates 104 against 94); and
+// neither set so long that a workgroup per four queries, or one workgroup's pass over the data,
+// would be.
 constexpr int64_t kSmallPairs = int64_t(1) << 26;
 constexpr int64_t kSmallSet = 16384;
 inline bool small_call(int64_t n, int64_t m) { return n <= kSmallSet && m <= kSmallSet && n * m <= kSmallPairs; }
