@@ -149,16 +149,21 @@ constexpr int kTile = 512;        // data points staged in LDS per tile (2 per t
 constexpr int kFixGrid = 1024;    // workgroups of the FP64 fix-up kernels
 constexpr int kCountBlock = 4096; // flags per compaction block (16 per thread)
 
-// Forwards that k_fwd_finish_small ends: few pairs, so that even if every query is a candidate or
+// Forwards that k_fwd_finish_small ends.  Few pairs, so that even if every query is a candidate or
 // a hit (passes over the data by one workgroup of four queries) the call is no longer than with
-// the general kernels (16,384 x 4,096: 40.6 us against 41.4, all hits 133 against 152, all
-// candidates 65 against 84), the line having been set when each query took a pass of its own
-// (10,240 x 10,240, twice the pairs: 43.8 against 45.6, but all candidates 104 against 94); and
-// neither set so long that a workgroup per four queries, or one workgroup's pass over the data,
-// would be.
+// the general kernels (8,192 x 8,192: 38.8 us against 37.8, all hits 126 against 194; 10,240 x
+// 10,240, twice the pairs: 43.8 against 45.6, but all candidates 104 against 94); neither set so
+// long that a workgroup per four queries, or one workgroup's pass over the data, would be; and,
+// since a pass gets longer with n while the launches that it saves matter less with n m, a limit
+// on n^2 m: with four neighbouring hits 12,288 x 4,096 takes 64 us and 16,384 x 2,048 70 (the
+// general kernels 44 and 43; without hits 31.9 and 24.6 against 35.2 and 33.5), but 16,384 x 4,096
+// 91, against 50, with nothing to gain without hits (40.4 against 41.6).
 constexpr int64_t kSmallPairs = int64_t(1) << 26;
 constexpr int64_t kSmallSet = 16384;
-inline bool small_call(int64_t n, int64_t m) { return n <= kSmallSet && m <= kSmallSet && n * m <= kSmallPairs; }
+constexpr int64_t kSmallPass = int64_t(5) << 37;
+inline bool small_call(int64_t n, int64_t m) {
+  return n <= kSmallSet && m <= kSmallSet && n * m <= kSmallPairs && n * n * m <= kSmallPass;
+}
 
 // Per-layout entry points (one translation unit per layout keeps builds parallel).
 #define IDW_DECLARE_LAYOUT(NAME)                                                 \
