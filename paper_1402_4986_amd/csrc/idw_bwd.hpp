@@ -308,15 +308,17 @@ __device__ __forceinline__ void bwdq_tile(const RecTile<T, DIM, kTile>& tl, int 
 }
 
 // Query sweep: writes part[c * m + i] = (P, Gx, Gy, Gz) in scaled units (double).  Q = 2; FP32
-// at 4 waves per SIMD (idw_phase.hpp), FP64 unrolled 4 deep at 2 or more.
-template <typename T, int Q>
+// at 4 waves per SIMD (idw_phase.hpp), FP64 unrolled 4 deep at 3 or more (general p at 2, where 3
+// would spill).  Left to itself the 3-D form with dp and dq took 176-188 registers, two waves per
+// SIMD: 131,072 x 131,072, p = 2, 16.39 ms against 15.74 with three.
+template <typename T, int Q, int PM>
 struct QueryTune {
   static constexpr int UNR = 4;
-  static constexpr int WMIN = sizeof(T) == 4 ? 4 : 2;
+  static constexpr int WMIN = sizeof(T) == 4 ? 4 : PM == PM_GEN ? 2 : 3;
   static constexpr int WMAX = sizeof(T) == 4 ? 4 : 8;
 };
 
-template <typename T, int DIM, int L, int PM, int Q, bool NDP, bool NDQ, typename Tune = QueryTune<T, Q>>
+template <typename T, int DIM, int L, int PM, int Q, bool NDP, bool NDQ, typename Tune = QueryTune<T, Q, PM>>
 __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(Tune::WMIN, Tune::WMAX))) void k_bwd_query(DevPts data, int64_t n, DevPts query, int64_t m,
                                                    int64_t chunk, T nhp, unsigned flags,
                                                    const double* __restrict__ hdr,
