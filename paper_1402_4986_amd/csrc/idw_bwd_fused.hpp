@@ -311,13 +311,14 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE, 8))) vo
 
 // Queries per wave: as many as the registers of 4 waves per SIMD hold.  16 in 2-D (48 sums) and
 // in 3-D (64 sums; 131,072 x 1M points, p = 2: 47.0 ms against 49.0 with 8); 8 where the scales
-// of the relative weights would make 16 spill.  With the 3-D X sums 16 fit once the FP64 sums
-// over lanes are left in memory (GSUM), and the staging, folding and row traffic of a tile are
-// shared by twice the queries (131,072 x 262,144, p = 2 with dx: 83 cycles per pair and wave with
-// 8 queries, 80 with 12, 74 with 16).
-template <int DIM, bool NDX, bool REL>
+// of the relative weights would make 16 spill, which for dz alone, without query sums and X sums,
+// they do not (65,536 x 65,536, p = 8: 1.18 ms against 1.28 with 8).  With the 3-D X sums 16 fit
+// once the FP64 sums over lanes are left in memory (GSUM), and the staging, folding and row
+// traffic of a tile are shared by twice the queries (131,072 x 262,144, p = 2 with dx: 83 cycles
+// per pair and wave with 8 queries, 80 with 12, 74 with 16).
+template <bool SUMS, bool NDX, bool REL>
 struct FusedRows {
-  static constexpr int R = REL ? 8 : 16;
+  static constexpr int R = REL && (SUMS || NDX) ? 8 : 16;
 };
 constexpr int kFusedWaves = 8;
 constexpr int kFlush = 4096;  // data points between the sums over lanes (64 per lane)
@@ -334,7 +335,7 @@ __device__ __forceinline__ double shfl_xor64(double v, int x) {
 }
 
 template <int DIM, int L, int PM, bool NDP, bool NDQ, bool NDX, bool REL, bool EXCL,
-          int R = FusedRows<DIM, NDX, REL>::R>
+          int R = FusedRows<NDP || NDQ, NDX, REL>::R>
 __global__ __launch_bounds__(64 * kFusedWaves) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_bwd_fused32(
     DevPts data, int64_t n, DevPts query, int64_t m, int64_t chunk, int groups, float nhp, unsigned,
     const double* __restrict__ hdr, const float* __restrict__ saved_z, const float* __restrict__ grad_out,

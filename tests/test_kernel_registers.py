@@ -40,3 +40,18 @@ template hipError_t idw::launch_bwd_query_t<double, 3, L_HYBRID, {pm}>(const Bwd
     assert len(ks) == 3
     for name, waves, spills in ks:
         assert waves >= 3 and spills == 0, (name, waves, spills)
+
+
+@pytest.mark.parametrize("dim", [2, 3])
+def test_dz_alone_with_relative_weights_has_16_queries_per_wave(tmp_path, dim):
+    ks = _kernels(tmp_path, f"""
+#include "idw_bwd_fused.hpp"
+using namespace idw;
+template hipError_t idw::launch_bwd_fused_t<float, {dim}, L_HYBRID, PM_GEN, true>(const BwdArgs&, int, int, int64_t,
+                                                                                 hipStream_t);
+""")
+    # <dim, layout, PM_GEN, no dp, no dq, no dx, relative, leave-one-out or not, queries per wave>
+    alone = [k for k in ks if f"k_bwd_fused32ILi{dim}ELi3ELi0ELb0ELb0ELb0ELb1E" in k[0]]
+    assert len(alone) == 2
+    for name, waves, spills in alone:
+        assert "ELi16EEE" in name and waves == 4 and spills == 0, (name, waves, spills)
