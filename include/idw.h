@@ -184,7 +184,8 @@ int idw_workspace_size(const idw_points* data, const idw_points* query, int32_t 
  *   workspace    device buffer of at least idw_workspace_size() bytes, 256-byte aligned;
  *                its contents on entry are irrelevant and on exit unspecified.
  * The workspace is in use until the enqueued work completes; concurrent calls must use
- * different workspaces. */
+ * different workspaces.  A call enqueues several kernels, so calls that two host threads make at
+ * the same time are concurrent even on one stream. */
 int idw_forward(const idw_points* data, const idw_points* query, double p, int32_t precision,
                 uint32_t flags, void* out_z, double* out_den, void* workspace,
                 size_t workspace_bytes, void* stream, const idw_config* cfg);

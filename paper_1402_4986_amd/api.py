@@ -7,6 +7,7 @@ sweeps, merges, FP64 fix-ups, reductions) runs in the library's HIP kernels.
 from __future__ import annotations
 
 import ctypes
+import threading
 from dataclasses import dataclass
 from typing import Optional, Sequence
 
@@ -86,15 +87,26 @@ def _stream_handle(device) -> int:
     return torch._C._cuda_getCurrentRawStream(device.index)
 
 
-_ws_cache: dict = {}
+class _Workspaces(threading.local):
+    """Each thread's own workspaces by (device, stream); they go when the thread ends."""
+
+    def __init__(self):
+        self.held = {}
+
+    def clear(self) -> None:
+        self.held.clear()
+
+
+_ws_cache = _Workspaces()
 
 
 def workspace(data: Points, query: Points, precision: str, cfg: Optional[IdwConfig] = None,
               backward: bool = True, need_dx: bool = False) -> torch.Tensor:
     """A device workspace for the forward (backward=False) or for forward and backward on
     these point sets, with room for the data-coordinate gradient when need_dx.  Cached per
-    (device, current stream) and grown on demand: calls enqueued on one stream run in order,
-    so they may share it, while work on another stream gets its own."""
+    (thread, device, current stream) and grown on demand: the calls that one thread enqueues on
+    one stream run in order, so they may share it; work on another stream gets its own, and so
+    does another thread, whose launches could come between those of a call."""
     return _workspace(_lib.load(), data.c(), query.c(), data.device, _stream_handle(data.device), precision, cfg,
                       backward, need_dx)
 
@@ -110,10 +122,11 @@ def _workspace(lib, dc: IdwPoints, qc: IdwPoints, device, stream: int, precision
     check(lib.idw_workspace_size(ctypes.byref(dc), ctypes.byref(qc), _lib.PRECISION_CODES[precision], flags,
                                  ctypes.byref(cfg) if cfg is not None else None, ctypes.byref(need)))
     key = (device, stream)
-    ws = _ws_cache.get(key)
+    held = _ws_cache.held
+    ws = held.get(key)
     if ws is None or ws.numel() < need.value:
         ws = torch.empty(max(need.value, 256), dtype=torch.uint8, device=device)
-        _ws_cache[key] = ws
+        held[key] = ws
     return ws
 
 
