@@ -212,15 +212,55 @@ static void choose_split(int64_t len, int64_t blocks, int want_split, int64_t un
   split = static_cast<int>(cdiv(len, chunk));
 }
 
-WsPlan plan_workspace(const idw_points* data, const idw_points* query, int precision,
-                      const idw_config* cfg) {
+// Appends a section of `bytes` to a layout of `off` bytes; returns its offset.
+static size_t take(size_t& off, size_t bytes) {
+  const size_t at = off;
+  off = al256(off + bytes);
+  return at;
+}
+
+// The forward's part of the plan (all that a forward call needs: the adjoint's search takes 1.2 us of
+// host time at 1M x 16,384, the rest 0.4).
+WsPlan plan_forward(const idw_points* data, const idw_points* query, int precision, const idw_config* cfg) {
   WsPlan w;
   const bool f64 = precision == IDW_FP64;
   const int64_t n = data->n, m = query->n;
-  // forward
   w.qf = (cfg && cfg->queries_per_lane) ? cfg->queries_per_lane : 4;
   choose_split(n, cdiv(m, kWG * w.qf), cfg ? cfg->split : 0, sizeof(double2), m, w.split_f, w.chunk_f, true);
-  // backward: query sweep over data chunks, data sweep over query chunks
+  w.nbbox = static_cast<int>(std::min<int64_t>(1024, cdiv(n, kWG)));
+  const int64_t nb = cdiv(m > 0 ? m : 1, kCountBlock);
+  size_t off = 0;
+  w.hdr = take(off, 512);
+  w.bbox = take(off, sizeof(double) * kBboxStride * static_cast<size_t>(w.nbbox));
+  w.flag = take(off, static_cast<size_t>(m));
+  w.bcnt = take(off, sizeof(int) * static_cast<size_t>(nb + 1));
+  w.list = take(off, sizeof(int) * static_cast<size_t>(m));
+  w.near_min = take(off, sizeof(unsigned long long) * static_cast<size_t>(m));
+  w.part_f = take(off, w.split_f > 1 ? sizeof(double2) * static_cast<size_t>(w.split_f) * m : 0);
+  w.fpart = take(off, sizeof(double4) * kFixGrid);
+  w.fix_cmax = static_cast<int>(std::min<int64_t>(kFixGrid, std::max<int64_t>(1, cdiv(n, 4096))));
+  // grid of the nearest-distance searches
+  w.grid_on = n >= kGridMinN && n <= kGridMaxN && m > 0 && !(cfg && cfg->near_search == 1);
+  if (w.grid_on) {
+    w.grid_ncell = std::min<int64_t>(kGridMaxCells, std::max<int64_t>(1, n / kGridPerCell));
+    const int64_t nb = cdiv(w.grid_ncell, kGridScanBlock);
+    w.grid_cnt = take(off, sizeof(int) * static_cast<size_t>(w.grid_ncell + 1));
+    w.grid_start = take(off, sizeof(int) * static_cast<size_t>(w.grid_ncell + 1));
+    w.grid_bsum = take(off, sizeof(int) * static_cast<size_t>(nb + 1));
+    w.grid_rec = take(off, 4 * (f64 ? sizeof(double) : sizeof(float)) * static_cast<size_t>(n));
+    w.grid_blist = take(off, sizeof(int) * static_cast<size_t>(m));
+  }
+  w.fwd_total = off;
+  return w;
+}
+
+// The whole plan: the adjoint's sections follow the forward's.
+WsPlan plan_workspace(const idw_points* data, const idw_points* query, int precision,
+                      const idw_config* cfg) {
+  WsPlan w = plan_forward(data, query, precision, cfg);
+  const bool f64 = precision == IDW_FP64;
+  const int64_t n = data->n, m = query->n;
+  // query sweep over data chunks, data sweep over query chunks
   w.qq = 2;
   choose_split(n, cdiv(m, kWG * w.qq), 0, sizeof(double4), m, w.split_q, w.chunk_q);
   w.qz = f64 ? 2 : 4;
@@ -271,47 +311,19 @@ WsPlan plan_workspace(const idw_points* data, const idw_points* query, int preci
       if (want >= rcap) break;
     }
   }
-  w.nbbox = static_cast<int>(std::min<int64_t>(1024, cdiv(n, kWG)));
   w.nwg_dp = static_cast<int>(cdiv(m, kWG));
-  const int64_t nb = cdiv(m > 0 ? m : 1, kCountBlock);
-  size_t off = 0;
-  auto take = [&](size_t bytes) {
-    const size_t at = off;
-    off = al256(off + bytes);
-    return at;
-  };
-  w.hdr = take(512);
-  w.bbox = take(sizeof(double) * kBboxStride * static_cast<size_t>(w.nbbox));
-  w.flag = take(static_cast<size_t>(m));
-  w.bcnt = take(sizeof(int) * static_cast<size_t>(nb + 1));
-  w.list = take(sizeof(int) * static_cast<size_t>(m));
-  w.near_min = take(sizeof(unsigned long long) * static_cast<size_t>(m));
-  w.part_f = take(w.split_f > 1 ? sizeof(double2) * static_cast<size_t>(w.split_f) * m : 0);
-  w.fpart = take(sizeof(double4) * kFixGrid);
-  w.fix_cmax = static_cast<int>(std::min<int64_t>(kFixGrid, std::max<int64_t>(1, cdiv(n, 4096))));
-  // grid of the nearest-distance searches
-  w.grid_on = n >= kGridMinN && n <= kGridMaxN && m > 0 && !(cfg && cfg->near_search == 1);
-  if (w.grid_on) {
-    w.grid_ncell = std::min<int64_t>(kGridMaxCells, std::max<int64_t>(1, n / kGridPerCell));
-    const int64_t nb = cdiv(w.grid_ncell, kGridScanBlock);
-    w.grid_cnt = take(sizeof(int) * static_cast<size_t>(w.grid_ncell + 1));
-    w.grid_start = take(sizeof(int) * static_cast<size_t>(w.grid_ncell + 1));
-    w.grid_bsum = take(sizeof(int) * static_cast<size_t>(nb + 1));
-    w.grid_rec = take(4 * (f64 ? sizeof(double) : sizeof(float)) * static_cast<size_t>(n));
-    w.grid_blist = take(sizeof(int) * static_cast<size_t>(m));
-  }
-  w.fwd_total = off;  // the forward uses only the sections above
-  w.part_q = take(sizeof(double4) * static_cast<size_t>(std::max(w.split_q, w.fused_ranges)) * m);
-  w.part_z = take(sizeof(double) * static_cast<size_t>(std::max(w.split_z, w.fused_groups)) * n);
-  w.slot_coef = take(sizeof(double) * static_cast<size_t>(m));
-  w.slot_hits = take(sizeof(int) * static_cast<size_t>(m));
-  w.slot_dp = take(sizeof(double) * static_cast<size_t>(m));
-  w.slot_z = take(sizeof(double) * static_cast<size_t>(m));
-  w.slot_den = take(sizeof(double) * static_cast<size_t>(m));
-  w.wg_dp = take(sizeof(double) * static_cast<size_t>(w.nwg_dp > 0 ? w.nwg_dp : 1));
+  size_t off = w.fwd_total;
+  w.part_q = take(off, sizeof(double4) * static_cast<size_t>(std::max(w.split_q, w.fused_ranges)) * m);
+  w.part_z = take(off, sizeof(double) * static_cast<size_t>(std::max(w.split_z, w.fused_groups)) * n);
+  w.slot_coef = take(off, sizeof(double) * static_cast<size_t>(m));
+  w.slot_hits = take(off, sizeof(int) * static_cast<size_t>(m));
+  w.slot_dp = take(off, sizeof(double) * static_cast<size_t>(m));
+  w.slot_z = take(off, sizeof(double) * static_cast<size_t>(m));
+  w.slot_den = take(off, sizeof(double) * static_cast<size_t>(m));
+  w.wg_dp = take(off, sizeof(double) * static_cast<size_t>(w.nwg_dp > 0 ? w.nwg_dp : 1));
   w.total = off;
-  w.part_x = take(sizeof(double) * static_cast<size_t>(std::max(w.split_z, w.fused_groups)) * n *
-                  static_cast<size_t>(data->dim));
+  w.part_x = take(off, sizeof(double) * static_cast<size_t>(std::max(w.split_z, w.fused_groups)) * n *
+                           static_cast<size_t>(data->dim));
   w.total_x = off;
   return w;
 }
@@ -588,10 +600,12 @@ int idw_workspace_size(const idw_points* data, const idw_points* query, int32_t 
   int rc = validate_common(data, query, 2.0, precision, flags & ~IDW_EXCLUDE_SELF);
   if (rc) return rc;
   if ((rc = validate_config(cfg))) return rc;
-  const WsPlan w = plan_workspace(data, query, precision, cfg);
-  *bytes = (flags & IDW_NEED_DX) ? w.total_x
-           : (flags & (IDW_NEED_DZ | IDW_NEED_DP | IDW_NEED_DQ)) ? w.total
-                                                                 : w.fwd_total;
+  if (flags & (IDW_NEED_DZ | IDW_NEED_DP | IDW_NEED_DQ | IDW_NEED_DX)) {
+    const WsPlan w = plan_workspace(data, query, precision, cfg);
+    *bytes = (flags & IDW_NEED_DX) ? w.total_x : w.total;
+  } else {
+    *bytes = plan_forward(data, query, precision, cfg).fwd_total;
+  }
   return IDW_OK;
 }
 
@@ -616,17 +630,24 @@ static int forward_impl(const idw_points* data, const idw_points* query, double 
   const int64_t m = query->n;
   if (m == 0) return IDW_OK;
   if (!out_z) return fail(IDW_EINVAL, "out_z is null");
-  WsPlan w = plan_workspace(data, query, precision, cfg);
+  WsPlan w = plan_forward(data, query, precision, cfg);
   if (static_scratch) {
     // Where the default data split's partial sums do not fit the scratch, take the largest
-    // split that does (the same result as idw_forward with that split in cfg).
+    // split that does (the same result as idw_forward with that split in cfg).  The sums shrink
+    // with the split, so that it is found by halving.
     if (w.fwd_total > kScratchBytes && !(cfg && cfg->split) && w.split_f > 1) {
       idw_config c{};
       if (cfg) c = *cfg;
-      for (c.split = w.split_f - 1; c.split >= 1; --c.split) {
-        w = plan_workspace(data, query, precision, &c);
-        if (w.fwd_total <= kScratchBytes) break;
+      auto with = [&](int split) {
+        c.split = split;
+        return plan_forward(data, query, precision, &c);
+      };
+      int fits = 1, above = w.split_f;  // unsplit, the last resort, is checked below
+      while (above - fits > 1) {
+        const int mid = fits + (above - fits) / 2;
+        (with(mid).fwd_total <= kScratchBytes ? fits : above) = mid;
       }
+      w = with(fits);
     }
     if (w.fwd_total > kScratchBytes)
       return fail(IDW_EWORKSPACE, "idw_forward_noalloc: these sizes need %zu bytes of scratch, above its %zu",

@@ -48,6 +48,7 @@ int validate_common(const idw_points* data, const idw_points* query, double p, i
                     uint32_t flags);
 int validate_config(const idw_config* cfg);
 int pmode_of(double p);
+WsPlan plan_forward(const idw_points* data, const idw_points* query, int precision, const idw_config* cfg);
 WsPlan plan_workspace(const idw_points* data, const idw_points* query, int precision,
                       const idw_config* cfg);
 DevPts dev_pts(const idw_points* P);
