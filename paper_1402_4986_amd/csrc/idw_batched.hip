@@ -301,7 +301,11 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
                                                 int nitems, int* __restrict__ counter,
                                                 const double* __restrict__ hdr,
                                                 double2* __restrict__ part) {
-  alignas(16) __shared__ char tile[2 * sizeof(RecTile<float, 3, kTile>)];
+  alignas(32) __shared__ char tile[2 * sizeof(RecTile<float, 3, kTile>)];  // of either dimension
+  static_assert(__alignof__(tile) >= alignof(RecTile<float, 2, kTile>) &&
+                    __alignof__(tile) >= alignof(RecTile<float, 3, kTile>) &&
+                    sizeof(tile) >= 2 * sizeof(RecTile<float, 2, kTile>),
+                "the tiles that kb_item keeps here");
   __shared__ int claim;
   for (;;) {
     const int w = kb_claim(counter, &claim);
@@ -338,7 +342,11 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
                                                     int* __restrict__ counter, const double* __restrict__ hdr,
                                                     double2* __restrict__ part,
                                                     const unsigned int* __restrict__ rmin) {
-  alignas(16) __shared__ char tile[2 * sizeof(RecTile<float, 3, kTile>)];
+  alignas(32) __shared__ char tile[2 * sizeof(RecTile<float, 3, kTile>)];  // of either dimension
+  static_assert(__alignof__(tile) >= alignof(RecTile<float, 2, kTile>) &&
+                    __alignof__(tile) >= alignof(RecTile<float, 3, kTile>) &&
+                    sizeof(tile) >= 2 * sizeof(RecTile<float, 2, kTile>),
+                "the tiles that kb_item keeps here");
   __shared__ int claim;
   for (;;) {
     const int w = kb_claim(counter, &claim);

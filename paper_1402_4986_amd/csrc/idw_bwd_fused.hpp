@@ -349,7 +349,8 @@ __global__ __launch_bounds__(64 * kFusedWaves) __attribute__((amdgpu_waves_per_e
   constexpr int NR = (R * NC + 7) / 8;          // rounds of 8 sums in the addition over lanes
   static_assert(R % 8 == 0 && R <= 64 && (NB & (NB - 1)) == 0, "whole runs of queries");
   __shared__ RecTile<float, 3, TILE> tile[2];
-  __shared__ float zred[kFusedWaves][TILE];     // per-wave dz sums of the tile; rows of the addition over lanes
+  alignas(16) __shared__ float zred[kFusedWaves][TILE];  // per-wave dz sums; rows of the addition over lanes
+  static_assert(__alignof__(zred) >= alignof(P4<float>), "flush reads four values at a time");
   __shared__ float xred[NDX ? kFusedWaves : 1][NDX ? DIM * TILE : 1];  // per-wave X sums
   // The FP64 sums over lanes: in LDS, or, where the X sums take it, in registers, or, where 16
   // queries with X sums leave none (3-D), in the query's partial itself.
