@@ -40,6 +40,7 @@ namespace idw {
 // tables of pow_t instead: the kernel fills them for the exponent nh - 1 when NDQ, else nh.
 template <int PM, bool NDQ, bool NDP, bool POW = false>
 __device__ __forceinline__ void wterms(float r2, float nhp, float& w, float& f, float& lg) {
+  static_assert(PM != PM_25, "the adjoint takes p = 2.5 as general p");
   if constexpr (PM == PM_GEN) {
     lg = __builtin_amdgcn_logf(r2);
     if constexpr (NDQ) {
@@ -65,11 +66,6 @@ __device__ __forceinline__ void wterms(float r2, float nhp, float& w, float& f, 
       const float t = __builtin_amdgcn_rcpf(r2);
       w = t * t;
       if constexpr (NDQ) f = t;
-    } else {  // PM_25
-      const float s = __builtin_amdgcn_rsqf(r2);
-      const float s2 = s * s;
-      w = s2 * __builtin_amdgcn_sqrtf(s);
-      if constexpr (NDQ) f = s2;
     }
   }
 }
@@ -129,6 +125,7 @@ __device__ __forceinline__ T wr_times(T t, T c, T f) {
 template <int PM, bool NDQ, bool NDP, int N>
 __device__ __forceinline__ void wterms_run(const float (&r2)[N], float nhp, float (&w)[N], float (&f)[N],
                                            float (&lg)[N]) {
+  static_assert(PM != PM_25, "the adjoint takes p = 2.5 as general p");
   run_begin();
   if constexpr (PM == PM_GEN) {
     const float e = NDQ ? nhp - 1.0f : nhp;
@@ -152,11 +149,6 @@ __device__ __forceinline__ void wterms_run(const float (&r2)[N], float nhp, floa
 #pragma unroll
       for (int i = 0; i < N; ++i) lg[i] = __builtin_amdgcn_logf(r2[i]);
     }
-    if constexpr (PM == PM_25) {
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int i = 0; i < N; ++i) f[i] = __builtin_amdgcn_sqrtf(w[i]);
-    }
   }
   run_end();
 #pragma unroll
@@ -173,10 +165,6 @@ __device__ __forceinline__ void wterms_run(const float (&r2)[N], float nhp, floa
     } else if constexpr (PM == PM_4) {
       f[i] = w[i];
       w[i] = w[i] * w[i];
-    } else {  // PM_25
-      const float s2 = w[i] * w[i];
-      w[i] = s2 * f[i];
-      f[i] = s2;
     }
   }
 }
