@@ -81,10 +81,11 @@ def _cfg(queries_per_lane: int = 0, split: int = 0, near_search: int = 0,
 
 
 def _stream_handle(device) -> int:
-    # The raw handle: building a Stream object for it costs 2 us of a call's 20.
-    if device.index is None:
+    # The raw handle where torch has it: building a Stream object costs 2 us of a call's 20.
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None or device.index is None:
         return torch.cuda.current_stream(device).cuda_stream
-    return torch._C._cuda_getCurrentRawStream(device.index)
+    return raw(device.index)
 
 
 class _Workspaces(threading.local):
