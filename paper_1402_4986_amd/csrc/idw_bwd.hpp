@@ -104,6 +104,19 @@ __device__ __forceinline__ void wterms(double r2, double nhp, double& w, double&
   }
 }
 
+// Whether the data-direction sums of an FP64 sweep take two queries' or points' reciprocals from
+// one (rcp64_w2), and wterms from such a reciprocal t = 1 / r2.
+template <typename T, int PM>
+struct PairRcp {
+  static constexpr bool on = sizeof(T) == 8 && (PM == PM_2 || PM == PM_4);
+};
+template <int PM, bool NDQ, bool NDP>
+__device__ __forceinline__ void wterms_rcp(double r2, double t, double& w, double& f, double& lg) {
+  if constexpr (NDP) lg = log2_t(r2);
+  w = PM == PM_4 ? t * t : t;
+  if constexpr (NDQ) f = t;
+}
+
 // Whether an FP64 sweep takes its general-p weights from the pow_t tables: only without dp
 // (whose log2 r2 the exp2/log2 route shares; a combined log2 and pow measured slower there,
 // its registers and LDS costing occupancy).
@@ -446,6 +459,26 @@ __device__ __forceinline__ void bwd_qmerge_block(int64_t block, const double4* _
   if (threadIdx.x == 0) wg_dp[block] = tot;
 }
 
+// Coordinate given to queries that a data-direction sweep leaves out (flagged for the FP64
+// fix-up, or past the end of the query chunk): far from every scaled data point, with r2
+// and every product of the pair terms finite, so that their zero factor a = 0 gives exact
+// zeros (an infinite coordinate would turn 0 * (q - x) into NaN).
+template <typename T>
+__device__ __forceinline__ T farT() {
+  return static_cast<T>(0x1p60);
+}
+
+// Scaled coordinate of a lane's data point in a data-direction sweep.  Where two points share a
+// reciprocal, one past the end lies far away (and far from the queries left out), and one at
+// infinity at 2^250, so that its partner's weights stay what they are.
+template <typename T, int PM>
+__device__ __forceinline__ T point_coord(T c, T s, bool there) {
+  if constexpr (PairRcp<T, PM>::on)
+    return there ? fmin(fmax(c * s, -0x1p250), 0x1p250) : -farT<T>();
+  else
+    return c * s;
+}
+
 // The whole tile of the data sweep in FP32 without a self pair, in runs (idw_phase.hpp).
 template <int DIM, int PM, int Q>
 __device__ __forceinline__ void bwdd_tile_run(const RecTile<float, DIM, kTile>& tl, const float (&xc)[Q][3], float nhp,
@@ -490,14 +523,28 @@ __device__ __forceinline__ void bwdd_tile(const RecTile<T, DIM, kTile>& tl, int6
     for (int ii = 0; ii < CH; ++ii) {
       const P4<T> d = tl.get(c0 + ii);
       const T a = (DIM == 3) ? d.w : d.z;
+      T w[Q];
 #pragma unroll
       for (int k = 0; k < Q; ++k) {
-        const T r2 = sqdist<T, DIM>(xc[k], d);
-        T w = weight_sweep<PM>(r2, nhp);
-        if constexpr (DIAG) {
-          if (it + c0 + ii == xj[k]) w = T(0);
+        w[k] = sqdist<T, DIM>(xc[k], d);
+        if constexpr (DIAG && PairRcp<T, PM>::on) {
+          if (it + c0 + ii == xj[k]) w[k] = T(1);
         }
-        az[k] = fmaT(a, w, az[k]);
+      }
+      if constexpr (PairRcp<T, PM>::on) {
+        static_assert(Q == 2, "two points per lane");
+        rcp64_w2(w[0], w[1]);
+      }
+#pragma unroll
+      for (int k = 0; k < Q; ++k) {
+        if constexpr (!PairRcp<T, PM>::on)
+          w[k] = weight_sweep<PM>(w[k], nhp);
+        else if constexpr (PM == PM_4)
+          w[k] *= w[k];
+        if constexpr (DIAG) {
+          if (it + c0 + ii == xj[k]) w[k] = T(0);
+        }
+        az[k] = fmaT(a, w[k], az[k]);
       }
     }
 #pragma unroll
@@ -538,19 +585,21 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(Tune::WMIN,
     T c[3] = {T(0), T(0), T(0)}, v = T(0);
     if (xj[k] < n) Loader<T, DIM, L>::data(data, xj[k], c, v);
 #pragma unroll
-    for (int d = 0; d < 3; ++d) xc[k][d] = c[d] * s;
+    for (int d = 0; d < 3; ++d) xc[k][d] = point_coord<T, PM>(c[d], s, xj[k] < n);
   }
   BlockSum<T> Zs[Q];
 #pragma unroll
   for (int k = 0; k < Q; ++k) Zs[k].zero();
 
   T rc[2][3], ra[2];
+  bool live[2];
   auto fetch = [&](int t) {
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       const int64_t i = ib + static_cast<int64_t>(t) * kTile + u * kWG + tid;
       rc[u][0] = rc[u][1] = rc[u][2] = padT<T>();
       ra[u] = T(0);
+      live[u] = false;
       if (i < ie) {
         const double D = saved_den[i];
         if (route[i] == F_FP32) {  // the others are left to the FP64 fix-up
@@ -560,13 +609,23 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(Tune::WMIN,
           rc[u][1] = c[1];
           rc[u][2] = c[2];
           ra[u] = static_cast<T>(static_cast<double>(grad_out[i]) / (D / unit));
+          live[u] = true;
         }
       }
     }
   };
   auto put = [&](int b) {
 #pragma unroll
-    for (int u = 0; u < 2; ++u) tile[b].put(u * kWG + tid, stage<T, DIM>(rc[u], ra[u], s));
+    for (int u = 0; u < 2; ++u) {
+      P4<T> r = stage<T, DIM>(rc[u], ra[u], s);
+      if constexpr (PairRcp<T, PM>::on) {
+        if (!live[u]) {
+          r.x = r.y = farT<T>();
+          if constexpr (DIM == 3) r.z = farT<T>();
+        }
+      }
+      tile[b].put(u * kWG + tid, r);
+    }
   };
 
   const int ntiles = static_cast<int>((ie - ib + kTile - 1) / kTile);
@@ -605,15 +664,6 @@ __device__ __forceinline__ void bwd_zmerge_block(int64_t block, const double* __
   grad_z[j] = static_cast<T>(h + l);
 }
 
-// Coordinate given to queries that a data-direction sweep leaves out (flagged for the FP64
-// fix-up, or past the end of the query chunk): far from every scaled data point, with r2
-// and every product of the pair terms finite, so that their zero factor a = 0 gives exact
-// zeros (an infinite coordinate would turn 0 * (q - x) into NaN).
-template <typename T>
-__device__ __forceinline__ T farT() {
-  return static_cast<T>(0x1p60);
-}
-
 // Data sweep with the data-coordinate gradient: lanes own Q data points (scaled coordinates
 // and value), query tiles (q_i, a_i) and Z_i are broadcast from LDS.  Accumulates, over
 // 64-record blocks as the data sweep,
@@ -647,7 +697,7 @@ __global__ __launch_bounds__(kWG) void k_bwd_datax(DevPts data, int64_t n, DevPt
     T c[3] = {T(0), T(0), T(0)}, v = T(0);
     if (xj[k] < n) Loader<T, DIM, L>::data(data, xj[k], c, v);
 #pragma unroll
-    for (int d = 0; d < 3; ++d) xc[k][d] = c[d] * s;
+    for (int d = 0; d < 3; ++d) xc[k][d] = point_coord<T, PM>(c[d], s, xj[k] < n);
     xv[k] = v;
   }
   BlockSum<T> Zs[Q], Xs[Q][3];
@@ -715,8 +765,34 @@ __global__ __launch_bounds__(kWG) void k_bwd_datax(DevPts data, int64_t n, DevPt
         const P4<T> d = tl[c0 + ii];
         const T zi = zt[c0 + ii];
         const T a = (DIM == 3) ? d.w : d.z;
+        T e[Q][3], q2[Q], t[Q];
+        if constexpr (PairRcp<T, PM>::on) {
+          static_assert(Q == 2, "two points per lane");
+#pragma unroll
+          for (int k = 0; k < Q; ++k) {
+            e[k][0] = d.x - xc[k][0];  // q - x
+            e[k][1] = d.y - xc[k][1];
+            q2[k] = e[k][0] * e[k][0];
+            q2[k] = fmaT(e[k][1], e[k][1], q2[k]);
+            if constexpr (DIM == 3) {
+              e[k][2] = d.z - xc[k][2];
+              q2[k] = fmaT(e[k][2], e[k][2], q2[k]);
+            }
+            t[k] = diag && it + c0 + ii == xj[k] ? T(1) : q2[k];  // the leave-one-out self pair
+          }
+          rcp64_w2(t[0], t[1]);
+        }
 #pragma unroll
         for (int k = 0; k < Q; ++k) {
+          if constexpr (PairRcp<T, PM>::on) {
+            const T aa = diag && it + c0 + ii == xj[k] ? T(0) : a;
+            const T aw = aa * (PM == PM_4 ? t[k] * t[k] : t[k]);
+            az[k] += aw;
+            const T v = aw * t[k] * (xv[k] - zi);
+#pragma unroll
+            for (int x = 0; x < DIM; ++x) ax[k][x] = fmaT(v, e[k][x], ax[k][x]);
+            continue;
+          }
           const T e0 = d.x - xc[k][0];  // q - x
           const T e1 = d.y - xc[k][1];
           T e2 = T(0);

@@ -66,6 +66,18 @@ __device__ __forceinline__ T bwdf_batch(const P4<T>* __restrict__ rec, int lane,
       j = jb + ((lane + s) & (kBatch - 1));
       valid = j < je;
     }
+    T rcp[Q];
+    if constexpr (PairRcp<T, PM>::on) {
+      static_assert(Q == 2, "two queries per lane");
+#pragma unroll
+      for (int k = 0; k < Q; ++k) {
+        rcp[k] = sqdist<T, DIM>(qc[k], d);
+        if constexpr (MASK) {
+          if (!valid || (excl && j == qi[k])) rcp[k] = T(1);
+        }
+      }
+      rcp64_w2(rcp[0], rcp[1]);
+    }
 #pragma unroll
     for (int k = 0; k < Q; ++k) {
       const T dx = qc[k][0] - d.x;
@@ -87,7 +99,10 @@ __device__ __forceinline__ T bwdf_batch(const P4<T>* __restrict__ rec, int lane,
         }
       }
       T w, f = T(0), lg = T(0);
-      wterms<PM, NDQ || NDX, NDP, PowTab<T, PM, NDP || NDX>::on>(r2, nhp, w, f, lg);
+      if constexpr (PairRcp<T, PM>::on)
+        wterms_rcp<PM, NDQ || NDX, NDP>(r2, rcp[k], w, f, lg);
+      else
+        wterms<PM, NDQ || NDX, NDP, PowTab<T, PM, NDP || NDX>::on>(r2, nhp, w, f, lg);
       const T t = w * c;
       if constexpr (NDP) ap[k] = fmaT(t, lg, ap[k]);
       if constexpr (NDQ || NDX) {
