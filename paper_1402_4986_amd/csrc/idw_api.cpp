@@ -179,10 +179,10 @@ constexpr int64_t kPartBudget = int64_t(1) << 31;
 // Splits `len` points into chunks (multiples of the tile) so that `blocks` x chunks is about
 // 16384 workgroups, at least 4 tiles per chunk (1 where 4 would leave fewer than 2048
 // workgroups) and at most kPartBudget bytes of partials (`unit` bytes per chunk and element
-// of the other set, `other` elements).  Every workgroup does the same work, and a grid of
-// 1024 workgroups (one per 1024-query block at 1M queries) on the 768 that are resident at
-// once loses about 7% to the last, partly empty round; with 16 times as many the loss is
-// below 1% (1M x 1M forward: 204.1 -> 189.2 ms).  Below a few tens of thousands of queries
+// of the other set, `other` elements).  Every workgroup does the same work, and a grid of one
+// or two rounds of the 1024 that are resident at once loses to the last, uneven one; with 16
+// rounds the loss is below 1% (1M x 1M forward, when 768 were resident: 204.1 ms with one
+// workgroup per 1024-query block, 189.2 with 16).  Below a few tens of thousands of queries
 // even 4-tile chunks leave most of the chip idle (10,240^2 forward call, FP64: 166 us with 5
 // chunks, 102 us with 20; 32,768^2 FP32: 268 -> 250 us), while from 65,536^2 on the longer
 // merge of finer splits outweighs the fuller grid (65,536^2: 789 us with 32 chunks, 803

@@ -320,8 +320,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE, 8))) vo
 // half a DPP add per pair, which also puts the SIMD's waves out of step (idw_phase.hpp;
 // measured 10 cycles per pair).  2-D p = 2 with dz, dp and dq: 11 plain instructions and two
 // transcendentals, 39.2 cycles per pair and wave at best, 41.7 for the loop body alone, 44.2
-// for the kernel; 1M x 1M: 350 ms with lanes owning queries and the rotation, 309 ms now; with
-// dx 462 -> 391, p = 1.5 404 -> 335, p = 8 (relative weights) 458 -> 402.
+// for the kernel; 1M x 1M: 350 ms with lanes owning queries and the rotation, 308 ms now; with
+// dx 462 -> 389, p = 1.5 404 -> 335, p = 8 (relative weights) 458 -> 403.
 // ---------------------------------------------------------------------------------------
 
 // Queries per wave: as many as the registers of 4 waves per SIMD hold.  16 in 2-D (48 sums) and

@@ -401,7 +401,8 @@ __device__ __forceinline__ double pow_t(double a) {
 // Coordinate of padding records in the sweeps' LDS tiles: +inf in FP32 (every weight form
 // gives exactly 0 there), a far finite value in FP64 (the one-step forms above give NaN at
 // +inf).  The forward sweep never visits them (its last tile is cut to the data count); in
-// the data-direction sweeps they carry a zero coefficient, so only their finiteness matters.
+// the data-direction sweeps they carry a zero coefficient, so only their finiteness matters
+// (where two points share a reciprocal they are moved to farT).
 template <typename T>
 __device__ __forceinline__ T padT() {
   return __builtin_huge_valf();
@@ -670,6 +671,8 @@ constexpr int64_t kSmallBoxMax = 16384;
 //  least 2^-21 (scaled units), which bounds every FP32 term and sum of the forward and
 //  adjoint sweeps below 2^125.  Thresholds are finite: for large p, (1e-6 * extent)^-p
 //  overflows, and an infinite threshold would pass an infinite denominator.
+//  In FP64 the lower threshold is 0, at p = 2 and 4 2^31 2^(-250 p): queries about 2^250 extents
+//  away, where a product of two r2 leaves the range (rcp64_w2).
 //  Relative weights (rel, FP32 with p >= kRelP): no weight is held in FP32 by itself, so the
 //  cap becomes the value bound alone (every query goes to FP64 when max|value| > kRelVmax),
 //  and the lower threshold is 2^(-10 p) (scaled units): a denominator above it has its

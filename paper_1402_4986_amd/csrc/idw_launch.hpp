@@ -23,7 +23,7 @@ struct FwdArgs {
   bool rel = false;    // FP32 relative weights (p >= kRelP): needs rmin
   const unsigned long long* rmin = nullptr;  // [m] nearest squared distance (FP32 bits)
   int split = 1;
-  int64_t chunk = 0;  // data points per split chunk (multiple of the tile)
+  int64_t chunk = 0;  // data points per split chunk (a multiple of 64; of the tile but in the finest splits)
   const double* hdr = nullptr;
   void* out_z = nullptr;
   double* out_den = nullptr;
