@@ -653,7 +653,7 @@ __device__ __forceinline__ FixSums fix_query(const DevPts& data, const DevPts& q
 
 // The same sums for the queries i[0] and i[1], each record read once.  At general p, whose weight is
 // a long chain of operations, hits go through as selects so that the two chains overlap (four
-// hits, 16,384 x 1,000, p = 1.7: 87 us against 97); the other weights keep the branch (all hits,
+// hits, 16,384 x 1,000, p = 1.7: 86 us against 97); the other weights keep the branch (all hits,
 // 8,192 x 8,192, p = 2: 126 us against 139).  red: a row per query.
 template <typename T, int DIM, int L, int PM>
 __device__ __forceinline__ void fix_pair(const DevPts& data, const DevPts& query, const int64_t (&i)[2], int64_t n,
@@ -676,12 +676,12 @@ __device__ __forceinline__ void fix_pair(const DevPts& data, const DevPts& query
       }
 #pragma unroll
       for (int k = 0; k < 2; ++k) {
-        const bool self = excl && j == i[k];
-        const double z = static_cast<double>(v);
-        acc[k].h += hit[k] && !self ? 1 : 0;
-        acc[k].hz += hit[k] && !self ? z : 0.0;
-        acc[k].num.add(hit[k] || self ? 0.0 : w[k] * z);
-        acc[k].den.add(hit[k] || self ? 0.0 : w[k]);
+        const bool self = excl && j == i[k], on = hit[k] && !self;
+        const double z = self ? 0.0 : static_cast<double>(v), u = hit[k] || self ? 0.0 : w[k];
+        acc[k].h += on ? 1 : 0;
+        acc[k].hz += on ? z : 0.0;
+        acc[k].num.add(u * z);  // of no account once there is a hit
+        acc[k].den.add(u);
       }
     } else {
 #pragma unroll
@@ -776,7 +776,7 @@ __global__ __launch_bounds__(kWG) void k_fwd_fixup(DevPts data, int64_t n, DevPt
 // 20 in place of 32.  A pass of one workgroup is a chain of loads and FP64 operations, 17 us (p = 2)
 // or 26 (p = 1.7) over 16,384 points: one for each of four neighbouring hits made a call of 16,384
 // x 1,000 slower (84 and 116 us) than the five kernels, which cut a query's data among workgroups
-// (80 and 107); in pairs it takes 66 and 87.
+// (80 and 107); in pairs it takes 66 and 86.
 template <typename T, int DIM, int L, int PM>
 __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_fwd_finish_small(DevPts data, int64_t n, DevPts query, int64_t m, int split,
                                                           double nhp, unsigned flags,

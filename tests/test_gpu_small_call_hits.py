@@ -95,3 +95,18 @@ def test_every_mixture_in_a_group(prec, dim, p, loo):
     ref = oracle.forward(x, z, q, p, self_index=np.arange(n) if loo else None)
     assert np.max(scaled_err(Z.cpu().numpy().astype(np.float64), ref)) <= TOL[prec]
     assert np.array_equal(np.isinf(D.cpu().numpy()), ref["H"] > 0)
+
+
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+@pytest.mark.parametrize("dim,p", [(2, 0.5), (2, 1.7), (3, 3.0)])
+def test_a_query_alone_has_the_same_bits(prec, dim, p):
+    # next to a point: recomputed in FP64, alone by one pass, beside hits and others two to a pass
+    n, m = 1024, 1000
+    x, z, q = rand_case(13, n, m, dim, prec)
+    q[::3] = x[:m:3]
+    q[1::5] = (x[1:m:5] + 2.0 ** -22).astype(np.float64 if prec == "f64" else np.float32)
+    d, qq = points(x, z, q, "hybrid", prec)
+    Z, D = api.forward(d, qq, p, prec)
+    for i in range(1, m, 5):
+        Zi, Di = api.forward(d, points(x, z, q[i:i + 1], "hybrid", prec)[1], p, prec)
+        assert torch.equal(Z[i:i + 1], Zi) and torch.equal(D[i:i + 1], Di), i
